@@ -24,20 +24,12 @@
 // weight panels in flight in registers.  Products run on
 // v_mfma_f32_16x16x32_bf16 with fp32 accumulation; X and W take the same
 // permutation of the contraction index.
+#include "gemm_common.hpp"
 #include "kernels.hpp"
 
 namespace rgd {
 
 namespace {
-
-RGD_DEV f32x4 mfma16x16x32(const u32x4& a, const u32x4& b, f32x4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
-                                                 __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-}
-
-RGD_DEV float silu(float g) { return g / (1.0f + __expf(-g)); }
-
-constexpr int kStep = 64;  // k values per pipeline step
 
 // X stage layouts.  Swizzled (the projections and SwiGLU): unpadded rows of
 // XS * 64 k values whose 16-byte chunks are XOR-swizzled, chunk c of row r at
@@ -50,7 +42,7 @@ constexpr int kStep = 64;  // k values per pipeline step
 // four MFMAs): rows padded by 16 bytes, unswizzled; the swizzled layout made
 // it 2-7% slower.
 template <int XS>
-RGD_DEV int xswz(int r) { return XS == 1 ? ((r & 7) ^ ((r >> 3) & 1)) : (r & 15); }
+RGD_DEV int xswz(int r) { return XS == 1 ? xswz1(r) : (r & 15); }
 
 // panels of N rows, rounded up to whole groups
 __host__ __device__ inline long long packed_panels(int N, int group) {
@@ -87,25 +79,8 @@ __global__ __launch_bounds__(NW * 64) void gemm_bf16_kernel(GemmArgs a) {
   // the argument segment and a full memory round trip before the first weight
   // request)
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), col16 = lane & 15;
-  // Workgroups are handed out in linear order (x fastest), round-robin over
-  // the chip's 8 XCDs, each with its own L2.  With several row blocks, the
-  // work is reordered so that the row blocks of one column group are 8 apart
-  // in that order: on one XCD at nearly the same time, so the later blocks'
-  // weight reads can hit the lines the first one brought into that L2.
   int gx = blockIdx.x, gy = blockIdx.y;
-  if (MT > 4 && gridDim.y > 1) {  // 64-row tiles are launched as one row block
-    const int G = gridDim.x, Y = gridDim.y;
-    const int lin = blockIdx.x + blockIdx.y * G;
-    const int full = (G / 8) * 8;  // column groups in whole octets
-    if (lin < full * Y) {
-      gy = (lin / 8) % Y;
-      gx = (lin / 8 / Y) * 8 + lin % 8;
-    } else {
-      const int rem = lin - full * Y, gr = G - full;
-      gx = full + rem % gr;
-      gy = rem / gr;
-    }
-  }
+  if (MT > 4) xcd_order(gx, gy);  // 64-row tiles are launched as one row block
   const int m0 = gy * (MT * 16);
   const int split = blockIdx.z;
   const int K = a.K, nst = K / kStep;
@@ -327,8 +302,9 @@ __global__ __launch_bounds__(NW * 64) void gemm_bf16_kernel(GemmArgs a) {
   }
 }
 
-// Row tiles per workgroup follow M (16, 32, 64 or 128 rows; larger M takes
-// several 128-row blocks, whose weight reads then largely hit in L2); the
+// Row tiles per workgroup follow M (16, 32, 64 or 128 rows; up to 256 rows, or
+// where the wide tiles do not apply, several 128-row blocks, whose weight reads
+// then largely hit in L2); the
 // 128-row tile stages X two 64-k steps at a time (LDS; one step per barrier
 // measured 13-18% slower for the LM head and the projections at 128 rows).
 // The tile height never changes a row's arithmetic.
@@ -412,14 +388,14 @@ int gemm_groups(int mode, int N) {
 // * up to 64 rows: split-K projections <1, 8, 4, 2>, SwiGLU <1, 4, 4, 4>;
 // * 65-128 rows (one 128-row tile): both <1, 8, 4> (128 columns per
 //   workgroup for split-K, 64 output features for SwiGLU);
-// * more rows: both <2, 8, 4> (256 columns / 128 features per workgroup: the
-//   two 128-row blocks of a column group then stream twice the weights per
-//   X stage they load), except split-K projections whose splits cover at most
-//   8 steps (the O projection), which keep one panel per wave with two steps
-//   in flight <1, 8, 2>;
-// * the LM head <4, 8, 2> at every height (512 columns per workgroup: the X
-//   rows every workgroup streams through LDS cost half as much per weight
-//   byte).
+// * 129-256 rows, split-K projections with fewer than 24 steps per split (the
+//   other GEMMs of more rows run the wide tiles of gemm_wide.hip): <2, 8, 4>
+//   (256 columns per workgroup: the two 128-row blocks of a column group then
+//   stream twice the weights per X stage they load), except where a split
+//   covers at most 8 steps (the O projection), which keeps one panel per wave
+//   with two steps in flight <1, 8, 2>;
+// * the LM head <4, 8, 2> (512 columns per workgroup: the X rows every
+//   workgroup streams through LDS cost half as much per weight byte).
 // A row's arithmetic is the same under every shape (same k order, same
 // split-K).
 namespace {
@@ -447,6 +423,10 @@ hipError_t launch_silu(const GemmArgs& a, hipStream_t s) {
 hipError_t gemm_bf16(const GemmArgs& a, hipStream_t s) {
   if (a.K % kStep != 0 || a.M < 1 || a.splits < 1 || a.splits > a.K / kStep) return hipErrorInvalidValue;
   const int g = gemm_groups(a.mode, a.N);
+  if (a.mode == GEMM_LOGITS && a.ntiles != g) return hipErrorInvalidValue;
+  if (a.mode != GEMM_STORE && a.splits != 1) return hipErrorInvalidValue;
+  if (gemm_wide_fits(a)) return gemm_wide(a, s);
+  if (a.summed) return hipErrorInvalidValue;
   switch (a.mode) {
     case GEMM_STORE:
       // (segments that are not 256-column aligned keep 128-column workgroups)
@@ -455,12 +435,10 @@ hipError_t gemm_bf16(const GemmArgs& a, hipStream_t s) {
       if (a.M > 128 && segments_aligned(a, 256)) return launch_store<2, 8, 4, 2>(a, s);
       return launch_store<1, 8, 4, 2>(a, s);
     case GEMM_SILU:
-      if (a.splits != 1) return hipErrorInvalidValue;
       if (a.M > 128) return launch_silu<2, 8, 4, 4>(a, s);
       if (a.M > 64) return launch_silu<1, 8, 4, 4>(a, s);
       return launch_silu<1, 4, 4, 4>(a, s);
     case GEMM_LOGITS:
-      if (a.splits != 1 || a.ntiles != g) return hipErrorInvalidValue;
       return launch_bf16<4, 8, 2, GEMM_LOGITS, 1>(a, g, s);
     default:
       return hipErrorInvalidValue;

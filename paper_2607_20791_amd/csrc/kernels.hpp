@@ -30,6 +30,10 @@ struct GemmArgs {
   // key (ordered value << 32 | ~index: larger value, then lower index, wins)
   unsigned long long* tilekey;
   int mode;
+  // GEMM_STORE, only where gemm_sums_splits says so: one output holding the
+  // sum of the splits in split order, started from y's own values when
+  // `accumulate` is set (the residual stream)
+  int summed, accumulate;
 };
 
 // bf16 weights are used in the packed panel layout (see gemm.hip); the LM
@@ -40,6 +44,11 @@ hipError_t pack_panels(const void* w, int N, int K, int group, void* out, hipStr
 size_t packed_elems(int N, int K, int group);
 int gemm_groups(int mode, int N);   // workgroups along N for a mode
 hipError_t gemm_bf16(const GemmArgs& a, hipStream_t s);
+// many rows (more than kWideRows): gemm_wide.hip
+constexpr int kWideRows = 128;
+bool gemm_wide_fits(const GemmArgs& a);
+bool gemm_sums_splits(const GemmArgs& a);
+hipError_t gemm_wide(const GemmArgs& a, hipStream_t s);
 hipError_t gemm_f32(const GemmArgs& a, hipStream_t s);
 
 // ------------------------------------------------------- row bookkeeping ----

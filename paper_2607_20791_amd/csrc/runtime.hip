@@ -406,7 +406,8 @@ int gemm(rgd_model* m, GemmArgs& g, hipStream_t s) {
   return RGD_OK;
 }
 
-int lm_head(rgd_model* m, const void* x, int ldx, int R, float* logits, hipStream_t s) {
+// keys: the argmax keys of the LM-head tiles are wanted (the probe's steps)
+int lm_head(rgd_model* m, const void* x, int ldx, int R, float* logits, hipStream_t s, bool keys = false) {
   GemmArgs g{};
   g.x = x;
   g.ldx = ldx;
@@ -419,7 +420,7 @@ int lm_head(rgd_model* m, const void* x, int ldx, int R, float* logits, hipStrea
   g.y = logits;
   g.ldy = m->cfg.vocab;
   g.tilemax = m->tilemax;
-  g.tilekey = m->bf16 ? m->tilekey : nullptr;
+  g.tilekey = m->bf16 && keys ? m->tilekey : nullptr;
   g.ntiles = m->ntiles;
   g.mode = GEMM_LOGITS;
   TimeScope ts(m, RGD_TIMER_LM_HEAD, s);
@@ -471,6 +472,12 @@ int forward_rows(rgd_model* m, rgd_kv* kv, const Rows& rows, const HostRows& h, 
                                         (float*)m->xn, s);
   };
   auto splits = [&](int mode, int N, int K) { return bf ? pick_splits(gemm_groups(mode, N), K) : 1; };
+  // many rows: the projection adds its splits to the residual stream itself
+  auto to_residual = [&](GemmArgs& g) {
+    if (!bf || !gemm_sums_splits(g)) return;
+    g.summed = g.accumulate = 1;
+    g.y = m->x;
+  };
   for (int l = 0; l < c.n_layers; ++l) {
     const rgd_layer_weights& L = m->layers[l];
     const KVLayout kvl = kv->layer(l);
@@ -493,9 +500,10 @@ int forward_rows(rgd_model* m, rgd_kv* kv, const Rows& rows, const HostRows& h, 
     g.ldy = g.N;
     g.split_stride = (long long)R * g.N;
     g.mode = GEMM_STORE;
+    if (bf) g.summed = gemm_sums_splits(g);
     RGD_TRY(gemm(m, g, s));
     if (bf)
-      HIP_OK(qkv_rope_store<bf16_t>(m->qkv_part, g.splits, g.split_stride, rows, Hq, Hkv, D, m->rope_cs, c.max_pos,
+      HIP_OK(qkv_rope_store<bf16_t>(m->qkv_part, g.summed ? 1 : g.splits, g.split_stride, rows, Hq, Hkv, D, m->rope_cs, c.max_pos,
                                     (bf16_t*)m->q, kvl, s));
     else
       HIP_OK(qkv_rope_store<float>(m->qkv_part, g.splits, g.split_stride, rows, Hq, Hkv, D, m->rope_cs, c.max_pos,
@@ -515,8 +523,9 @@ int forward_rows(rgd_model* m, rgd_kv* kv, const Rows& rows, const HostRows& h, 
     o.ldy = d;
     o.split_stride = (long long)R * d;
     o.mode = GEMM_STORE;
+    to_residual(o);
     RGD_TRY(gemm(m, o, s));
-    HIP_OK(norm(m->o_part, o.splits, L.ffn_norm));
+    HIP_OK(norm(m->o_part, o.summed ? 0 : o.splits, L.ffn_norm));
     // SwiGLU: act = silu(W_gate xn) * (W_up xn)
     GemmArgs f{};
     f.x = m->xn;
@@ -545,9 +554,10 @@ int forward_rows(rgd_model* m, rgd_kv* kv, const Rows& rows, const HostRows& h, 
     dn.ldy = d;
     dn.split_stride = (long long)R * d;
     dn.mode = GEMM_STORE;
+    to_residual(dn);
     RGD_TRY(gemm(m, dn, s));
     const void* next_gain = l + 1 < c.n_layers ? m->layers[l + 1].attn_norm : (const void*)m->final_norm;
-    HIP_OK(norm(m->down_part, dn.splits, next_gain));
+    HIP_OK(norm(m->down_part, dn.summed ? 0 : dn.splits, next_gain));
     HIP_OK(readout(l + 1));
   }
   return RGD_OK;
@@ -1220,7 +1230,7 @@ int probe_impl(rgd_model* m, rgd_kv* kv, const float* last_logits, const rgd_tab
     // row r feeds token j-1 of its prompt's probe (probe_tokens[prompt[r]][j-2])
     Rows rows = device_rows(m, kv, R, j - 2, false);
     RGD_TRY(forward_rows(m, kv, rows, h, probe_tokens + (j - 2), k, s, embedded, nullptr, m->d_prompt));
-    RGD_TRY(lm_head(m, m->xn, m->cfg.d_model, R, m->logits, s));
+    RGD_TRY(lm_head(m, m->xn, m->cfg.d_model, R, m->logits, s, true));
     RGD_TRY(step(m->logits, R, j, true));
     if (pipelined) {
       HIP_OK(spin_wait(m->poll_done));

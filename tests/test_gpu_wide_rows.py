@@ -1,0 +1,84 @@
+"""GEMM tiles of many rows against those of few, bit for bit.
+
+A row's arithmetic does not depend on how many rows share a launch, so a
+prompt prefilled 64 tokens at a time (the tiles that the oracle parity tests
+pin) and in chunks of hundreds or thousands of rows (256-row tiles, partial
+last tiles, split-K partials added by the GEMM itself or by its consumer) gives
+the same logits and the same K/V, and so does the LM head row by row."""
+import pytest
+
+from tests.gpu_common import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def rgd():
+    import paper_2607_20791_amd as m
+    return m
+
+
+def _world(t, seed, d, ffn, hq, hk, V, layers=1):
+    g = t.Generator(device="cuda").manual_seed(seed)
+
+    def w(*s, std=0.02):
+        return (t.randn(*s, generator=g, device="cuda") * std).bfloat16()
+    one = t.ones(d, device="cuda")
+    top = {"embed": w(V, d, std=1.0), "final_norm": one, "lm_head": w(V, d)}
+    shapes = {"wq": (hq * 128, d), "wk": (hk * 128, d), "wv": (hk * 128, d), "wo": (d, hq * 128),
+              "w_gate": (ffn, d), "w_up": (ffn, d), "w_down": (d, ffn)}
+    return top, [dict({n: w(*s) for n, s in shapes.items()}, attn_norm=one, ffn_norm=one) for _ in range(layers)]
+
+
+def _prefill(rgd, t, world, dims, tokens, max_rows):
+    d, ffn, hq, hk, V = dims
+    B, n = tokens.shape
+    top, layers = world
+    cfg = rgd.ModelConfig(len(layers), d, hq, hk, 128, ffn, V, rgd.DTYPE_BF16, 1e-5, 500000.0, n)
+    m = rgd.Model(cfg, top, layers, max_rows)
+    z = lambda *s: t.zeros(s, dtype=t.bfloat16, device="cuda")  # noqa: E731
+    kv = rgd.KV(m, B, n, 0, 16, z(len(layers), B, hk, n, 128), z(len(layers), B, hk, (n + 63) // 64, 128, 64),
+                z(len(layers), 1, hk, 16, 128), z(len(layers), 1, hk, 128, 16))
+    last = t.empty(B, V, device="cuda")
+    rgd.prefill_kv(m, kv, tokens, 0, last)
+    t.cuda.synchronize()
+    return last, kv.prefix_k, kv.prefix_v
+
+
+# (d, ffn, heads, kv heads, vocab), prompts, tokens, max_rows of the wide run:
+# one partial tile past 256 rows; 2 + 1 tiles with an odd step count per split
+# (88 steps over 8 splits) and an uneven split (22 steps over 4); chunks whose
+# projections add their splits themselves (2100 rows, a 52-row last tile); rows
+# of several prompts in one chunk
+CASES = [((1024, 2816, 8, 4, 512), 1, 257, 300), ((1024, 5632, 8, 2, 512), 1, 700, 513),
+         ((1024, 1408, 8, 2, 512), 1, 600, 600), ((1024, 3584, 8, 2, 512), 1, 2100, 2100),
+         ((4096, 1152, 32, 8, 512), 3, 230, 700)]
+
+
+@pytest.mark.parametrize("dims,prompts,n,rows", CASES)
+def test_prefill_chunk_size_does_not_matter(rgd, dims, prompts, n, rows):
+    t = torch()
+    world = _world(t, n, *dims)
+    g = t.Generator(device="cuda").manual_seed(n + 1)
+    tokens = t.randint(0, dims[4], (prompts, n), generator=g, device="cuda", dtype=t.int32)
+    few = _prefill(rgd, t, world, dims, tokens, 64)
+    wide = _prefill(rgd, t, world, dims, tokens, rows)
+    for a, b in zip(few, wide):
+        assert t.isfinite(a.float()).all() and t.equal(a, b)
+
+
+@pytest.mark.parametrize("R,V", [(129, 1100), (256, 512), (257, 4), (300, 64), (513, 1348)])
+def test_lm_head_rows_alone_and_together(rgd, R, V):
+    """Vocabularies that end inside a 64-column group and inside a 512-column workgroup; rows past one tile."""
+    t = torch()
+    dims = (1024, 128, 1, 1, V)
+    top, layers = _world(t, R, *dims)
+    m = rgd.Model(rgd.ModelConfig(1, 1024, 1, 1, 128, 128, V, rgd.DTYPE_BF16, 1e-5, 500000.0, 64), top, layers, R)
+    h = t.randn(R, 1024, generator=t.Generator(device="cuda").manual_seed(R), device="cuda").bfloat16()
+    out = t.full((R + 1, V), -7.0, device="cuda")
+    rgd.kernel_lm_head(m, h, out[:R])
+    rows = t.empty(R, V, device="cuda")
+    for r in range(0, R, 50):
+        rgd.kernel_lm_head(m, h[r:r + 50].contiguous(), rows[r:r + 50])
+    t.cuda.synchronize()
+    assert t.equal(out[:R], rows) and bool((out[R] == -7.0).all())
