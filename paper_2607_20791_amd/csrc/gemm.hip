@@ -325,43 +325,6 @@ hipError_t launch_bf16(const GemmArgs& a, int ngroups, hipStream_t s) {
   return hipGetLastError();
 }
 
-// ----------------------------------------------------------------- fp32 ----
-// Plain fp32 path for small fp32 models: one thread per output element.
-template <int MODE>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a) {
-  const int n = blockIdx.x * 256 + threadIdx.x;
-  const int m = blockIdx.y;
-  const float* x = (const float*)a.x + (long long)m * a.ldx;
-  const int K = a.K;
-  const bool ok = n < a.N;
-  const int nc = min(n, a.N - 1);
-  float acc = 0.f, acc2 = 0.f;
-  if (MODE == GEMM_SILU) {
-    const float* wg = (const float*)a.seg[0].w + (long long)nc * K;
-    const float* wu = (const float*)a.seg[1].w + (long long)nc * K;
-    for (int k = 0; k < K; ++k) {
-      acc += x[k] * wg[k];
-      acc2 += x[k] * wu[k];
-    }
-    if (ok) ((float*)a.y)[(long long)m * a.ldy + n] = silu(acc) * acc2;
-    return;
-  }
-  int si = 0;
-  if (a.nseg > 1 && nc >= a.seg[1].n0) si = 1;
-  if (a.nseg > 2 && nc >= a.seg[2].n0) si = 2;
-  const float* w = (const float*)a.seg[si].w + (long long)(nc - a.seg[si].n0) * K;
-  for (int k = 0; k < K; ++k) acc += x[k] * w[k];
-  float* Y = (float*)a.y;
-  if (MODE == GEMM_STORE) {
-    if (ok) Y[(long long)m * a.ldy + n] = acc;
-  } else {
-    if (ok) Y[(long long)m * a.ldy + n] = acc;
-    // 64 consecutive columns form one wave: its max is that tile's max
-    const float v = wave_max(ok ? acc : -INFINITY);
-    if ((threadIdx.x & 63) == 0 && ok) a.tilemax[(long long)m * a.ntiles + n / 64] = v;
-  }
-}
-
 }  // namespace
 
 hipError_t pack_panels(const void* w, int N, int K, int group, void* out, hipStream_t s) {
@@ -443,19 +406,6 @@ hipError_t gemm_bf16(const GemmArgs& a, hipStream_t s) {
     default:
       return hipErrorInvalidValue;
   }
-}
-
-hipError_t gemm_f32(const GemmArgs& a, hipStream_t s) {
-  dim3 grid((a.N + 255) / 256, a.M);
-  switch (a.mode) {
-    case GEMM_STORE:
-      hipLaunchKernelGGL(gemm_f32_kernel<GEMM_STORE>, grid, dim3(256), 0, s, a); break;
-    case GEMM_SILU:
-      hipLaunchKernelGGL(gemm_f32_kernel<GEMM_SILU>, grid, dim3(256), 0, s, a); break;
-    default:
-      hipLaunchKernelGGL(gemm_f32_kernel<GEMM_LOGITS>, grid, dim3(256), 0, s, a); break;
-  }
-  return hipGetLastError();
 }
 
 }  // namespace rgd

@@ -1,0 +1,55 @@
+"""fp32 kernels at the edges of their tiles, against the oracle.
+
+The projections multiply 16-wide tiles of rows, columns and k; head sizes,
+widths and row counts here leave remainders in each, and one FFN width is not a
+multiple of 4 (the general kernel).  Tolerance 1e-5 of each row's largest value,
+as for the tiny fp32 decoder (fp32 sums of up to 1100 terms)."""
+import numpy as np
+import pytest
+
+import synth
+from oracle.model import Decoder, KVCache
+from tests.gpu_common import rel_err, torch
+
+pytestmark = pytest.mark.gpu
+
+BASE = synth.scaled(synth.TINY_FP32, name="f32-shapes", weight_std=0.1)
+# d_model, heads, kv heads, head_dim, ffn, vocab
+SHAPES = [(36, 3, 1, 8, 52, 68), (40, 5, 5, 16, 50, 260), (260, 8, 1, 32, 1100, 132), (1028, 2, 1, 128, 516, 64)]
+
+
+@pytest.fixture(scope="module")
+def rgd():
+    import paper_2607_20791_amd as m
+    return m
+
+
+@pytest.mark.parametrize("prompts,n", [(1, 1), (1, 17), (3, 11), (2, 65)])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_prefill_and_decode_f32(rgd, shape, prompts, n):
+    t = torch()
+    from paper_2607_20791_amd import session
+    d, hq, hk, D, ffn, V = shape
+    steps = 3
+    w = synth.scaled(BASE, d_model=d, n_heads=hq, n_kv_heads=hk, head_dim=D, ffn=ffn, vocab=V, n_prompts=prompts,
+                     prompt_len=n)
+    weights = synth.model_weights(w)
+    toks = synth.prompt_tokens(w)
+    rows = prompts * n
+    m = session.build_model(weights, max_rows=max(rows, prompts), max_pos=n + steps)
+    kv = session.alloc_kv(m, w, max_prompts=prompts, max_prefix=n, n_pages=prompts)
+    last = t.empty(prompts, V, device="cuda")
+    rgd.prefill_kv(m, kv, session.to_device(toks), 0, last)
+    forced = synth.forced_history(w, prompts, steps)
+    tap = t.empty(steps, prompts, V, device="cuda")
+    out = t.empty(prompts, 1, steps, dtype=t.int32, device="cuda")
+    rgd.sample_continuations(m, kv, last, list(range(prompts)), 1, steps, 1.0, 0.1,
+                             t.arange(prompts, device="cuda"), out, forced=session.to_device(forced), logits_tap=tap)
+    got_last, got = last.cpu().numpy(), tap.cpu().numpy()
+    dec = Decoder(weights)
+    for b in range(prompts):
+        cache, tail = KVCache(w.n_layers), KVCache(w.n_layers)
+        assert rel_err(got_last[b], dec.prefill(toks[b], cache)).max() <= 1e-5
+        for s in range(1, steps):
+            ref = dec.decode(int(forced[b, s - 1]), cache, tail)
+            assert rel_err(got[s, b], np.asarray(ref)).max() <= 1e-5, (b, s)
