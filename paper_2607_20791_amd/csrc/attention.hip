@@ -419,247 +419,246 @@ __global__ __launch_bounds__(NW * 64) void attn_prefix_kernel(AttnArgs a) {
   }
 }
 
-// Vector path: one workgroup per (chunk, KV head, row); one position per
-// thread for the scores, one (head, dim) pair per thread for the weighted sum.
-// PREFIX selects the shared prompt KV, otherwise the row's paged tail.
-constexpr int kChunk = 256;
+// fp32 attention of small decoders, on the vector units.  A step reads a few
+// hundred KB that sit in the caches, so both kernels are bound by their chain of
+// memory round trips and barriers: four lanes share a position's K row and hold
+// all their loads of it at once, the first V block is requested before the
+// softmax, and one wave does a head's softmax without workgroup barriers.
+// Measured at 16 rows, 64 prefix positions, up to 32 tail positions (a loop over
+// the row with one load at a time, block-wide reductions / this): prefix 27.1 /
+// 6.8 us, tail and merge 10.8 / 7.4 us; 1024 prefill rows 55.9 / 11.7 us.
+constexpr int kChunk = 256;      // positions per prefix split and per tail block
+constexpr int kMaxSplits = 40;
 
-template <typename T, bool PREFIX>
-__global__ __launch_bounds__(256) void attn_vec_kernel(AttnArgs a) {
-  const int c = blockIdx.x, g = blockIdx.y, r = blockIdx.z;
-  const int D = a.D, G = a.Hq / a.Hkv;
-  __shared__ float qs[8][256];
-  __shared__ float sc[8][kChunk];
-  __shared__ float red[4];
-  const int end = PREFIX ? a.rows.plen[r] : a.tail_len;
-  const int clen = PREFIX ? a.split_len : a.tail_chunk;
-  const int lo = c * clen;
-  const int hi = min(lo + clen, end);
-  const long long pstride = (long long)a.Hkv * D;
-  for (int i = threadIdx.x; i < G * D; i += 256)
-    qs[i / D][i % D] = load_f((const T*)a.q + ((long long)r * a.Hq + g * G) * D + i);
-  __syncthreads();
+// 8 consecutive elements starting at p (16-byte aligned)
+RGD_DEV void load8(const float* p, float* out) {
+  const f32x4 a = *(const f32x4*)p, b = *(const f32x4*)(p + 4);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    out[i] = a[i];
+    out[4 + i] = b[i];
+  }
+}
 
-  const long long bg = (long long)a.rows.prompt[r] * a.Hkv + g;
-  auto k_row = [&](int pos) -> const T* {
-    if (PREFIX) return (const T*)a.kv.prefix_k + (bg * a.kv.P + pos) * D;
-    const int ps = a.kv.page_size;
-    const int page = a.rows.pages[(long long)r * a.rows.max_pages + pos / ps];
-    return (const T*)a.kv.pool_k + (((long long)page * a.Hkv + g) * ps + pos % ps) * D;
-  };
-  auto v_at = [&](int pos, int d) -> float {
-    if (PREFIX)
-      return load_f((const T*)a.kv.prefix_v + ((bg * (a.kv.VP / 64) + pos / 64) * D + d) * 64 + pos % 64);
-    const int ps = a.kv.page_size;
-    const int page = a.rows.pages[(long long)r * a.rows.max_pages + pos / ps];
-    return load_f((const T*)a.kv.pool_v + (((long long)page * a.Hkv + g) * D + d) * ps + pos % ps);
-  };
-
-  const float scale = rsqrtf(float(D));
-  const int t = threadIdx.x;
-  const int pos = lo + t;
-  if (t < kChunk) {
-    if (pos < hi) {
-      const T* kr = k_row(pos);
-      float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      for (int d = 0; d < D; ++d) {
-        const float kd = load_f(kr + d);
-        for (int h = 0; h < G; ++h) acc[h] += qs[h][d] * kd;
+// q . k for n <= kChunk positions and G <= 8 heads into sc[h][position]:
+// position p by lanes 4 p .. 4 p + 3, lane j the float4s j, j + 4, .. of the row.
+// k_row(p) gives the row of position p.
+template <int D, typename F>
+RGD_DEV void f32_scores(const float (&qs)[8][D], float (&sc)[8][kChunk], int n, int G, float scale, F k_row) {
+  constexpr int NV = (D + 15) / 16;
+  const int j = threadIdx.x & 3;
+  for (int p0 = 0; p0 < n; p0 += 64) {
+    const int p = p0 + (threadIdx.x >> 2);
+    const float* kr = k_row(min(p, n - 1));
+    f32x4 k[NV];
+#pragma unroll
+    for (int i = 0; i < NV; ++i) k[i] = *(const f32x4*)(kr + min(j * 4 + i * 16, D - 4));
+#pragma unroll
+    for (int h = 0; h < 8; ++h) {
+      if (h >= G) break;
+      float dot = 0.f;
+#pragma unroll
+      for (int i = 0; i < NV; ++i) {
+        const f32x4 q = *(const f32x4*)&qs[h][min(j * 4 + i * 16, D - 4)];
+        const float t = q[0] * k[i][0] + q[1] * k[i][1] + q[2] * k[i][2] + q[3] * k[i][3];
+        dot += j * 4 + i * 16 < D ? t : 0.f;
       }
-      for (int h = 0; h < G; ++h) sc[h][t] = acc[h] * scale;
-    } else {
-      for (int h = 0; h < G; ++h) sc[h][t] = -INFINITY;
+      dot += __shfl_xor(dot, 1, 64);
+      dot += __shfl_xor(dot, 2, 64);
+      if (j == 0) sc[h][p] = p < n ? dot * scale : -INFINITY;
     }
   }
+}
+
+// One head's block of n scores by one wave: the block's exponentials relative to
+// the new running maximum replace them; m and l are the running maximum and
+// sum (alpha: factor of what was summed before).
+RGD_DEV void f32_softmax(float (&sc)[kChunk], int n, float& m, float& l, float& alpha) {
+  const int lane = threadIdx.x & 63;
+  float v[kChunk / 64], mx = m;
+#pragma unroll
+  for (int i = 0; i < kChunk / 64; ++i) {
+    const int p = lane + 64 * i;
+    v[i] = p < n ? sc[p] : -INFINITY;
+    mx = fmaxf(mx, v[i]);
+  }
+  mx = wave_max(mx);
+  float sum = 0.f;
+#pragma unroll
+  for (int i = 0; i < kChunk / 64; ++i) {
+    const int p = lane + 64 * i;
+    const float e = v[i] == -INFINITY ? 0.f : __expf(v[i] - mx);
+    if (p < n) sc[p] = e;
+    sum += e;
+  }
+  alpha = m == -INFINITY ? 0.f : __expf(m - mx);
+  l = l * alpha + wave_sum(sum);
+  m = mx;
+}
+
+// acc[h] += weights * V of dimension d over blocks of 8 positions part * 8,
+// + 8 * parts, ..; the first block's values are given.  v_at(p) points at the
+// values of positions p .. p + 7 (values past n are not used).
+template <int PARTS, typename F>
+RGD_DEV void f32_weighted(const float (&sc)[8][kChunk], int n, int G, int part, float (&v)[8], float (&acc)[8], F v_at) {
+  for (int b0 = part * 8; b0 < n; b0 += PARTS * 8) {
+    float nv[8];
+    load8(v_at(min(b0 + PARTS * 8, (n - 1) & ~7)), nv);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float ve = b0 + e < n ? v[e] : 0.f;
+#pragma unroll
+      for (int h = 0; h < 8; ++h)
+        if (h < G) acc[h] += sc[h][min(b0 + e, n - 1)] * ve;
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = nv[e];
+  }
+}
+
+// One workgroup per (prefix split, KV head, row).
+template <int D>
+__global__ __launch_bounds__(256) void attn_prefix_f32_kernel(AttnArgs a) {
+  constexpr int PARTS = 256 / D;
+  const int c = blockIdx.x, g = blockIdx.y, r = blockIdx.z;
+  const int G = a.Hq / a.Hkv, tid = threadIdx.x, wave = tid >> 6;
+  __shared__ __attribute__((aligned(16))) float qs[8][D];
+  __shared__ float sc[8][kChunk];
+  __shared__ float accx[PARTS][8][D];
+  __shared__ float ml[2][8];
+  const int lo = c * a.split_len, n = min(a.split_len, a.rows.plen[r] - lo);
+  const long long bg = (long long)a.rows.prompt[r] * a.Hkv + g;
+  const float* kp = (const float*)a.kv.prefix_k + (bg * a.kv.P + lo) * D;
+  const int d = tid % D, part = tid / D;
+  // (split lengths are multiples of 64: lo starts a 64-position V block)
+  const float* vp = (const float*)a.kv.prefix_v + (bg * (a.kv.VP / 64) + lo / 64) * D * 64 + (long long)d * 64;
+  auto v_at = [&](int p) -> const float* { return vp + (long long)(p >> 6) * D * 64 + (p & 63); };
+  for (int i = tid; i < G * D; i += 256) qs[i / D][i % D] = ((const float*)a.q)[((long long)r * a.Hq + g * G) * D + i];
+  float v[8], acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  if (n > 0) load8(v_at(min(part * 8, (n - 1) & ~7)), v);
   __syncthreads();
-  float mh[8], lh[8];
-  for (int h = 0; h < G; ++h) {
-    const float mx = block_max(sc[h][t], red);
-    const float e = mx == -INFINITY ? 0.f : __expf(sc[h][t] - mx);
-    __syncthreads();
-    sc[h][t] = e;
-    mh[h] = mx;
-    lh[h] = block_sum(e, red);
+  if (n > 0) f32_scores<D>(qs, sc, n, G, rsqrtf(float(D)), [&](int p) { return kp + (long long)p * D; });
+  __syncthreads();
+  for (int h = wave; h < G; h += 4) {
+    float m = -INFINITY, l = 0.f, alpha;
+    if (n > 0) f32_softmax(sc[h], n, m, l, alpha);
+    ml[0][h] = m;
+    ml[1][h] = l;
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < G * D; i += 256) {
-    const int h = i / D, d = i % D;
-    float acc = 0.f;
-    for (int p = lo; p < hi; ++p) acc += sc[h][p - lo] * v_at(p, d);
-    const long long idx = ((long long)c + (PREFIX ? 0 : a.splits)) * a.rows.R + r;
-    const int head = g * G + h;
-    a.part_o[(idx * a.Hq + head) * D + d] = lh[h] > 0.f ? acc / lh[h] : 0.f;
-    if (d == 0) a.part_lse[idx * a.Hq + head] = lh[h] > 0.f ? mh[h] + __logf(lh[h]) : -INFINITY;
+  if (n > 0) f32_weighted<PARTS>(sc, n, G, part, v, acc, v_at);
+#pragma unroll
+  for (int h = 0; h < 8; ++h)
+    if (h < G) accx[part][h][d] = acc[h];
+  __syncthreads();
+  for (int i = tid; i < G * D; i += 256) {
+    const int h = i / D, dd = i % D;
+    float o = 0.f;
+#pragma unroll
+    for (int p = 0; p < PARTS; ++p) o += accx[p][h][dd];
+    const float l = ml[1][h];
+    const long long idx = ((long long)c * a.rows.R + r) * a.Hq + g * G + h;
+    a.part_o[idx * D + dd] = l > 0.f ? o / l : 0.f;
+    if (dd == 0) a.part_lse[idx] = l > 0.f ? ml[0][h] + __logf(l) : -INFINITY;
   }
 }
 
 // Tail attention fused with the merge of all partials: one workgroup per
-// (row, KV head).  The row's own tail positions are attended on the vector
-// units (each K row and each V value is loaded once and used by all G query
-// heads of the KV head), then the prefix-split partials of those heads are
-// merged with the tail in log-sum-exp form and the final output is written.
-constexpr int kTailBlk = 256;
-constexpr int kMaxSplits = 40;
-
-// 8 consecutive elements starting at p (16-byte aligned for bf16, 32 for fp32)
-RGD_DEV void load8(const bf16_t* p, float* out) {
-  const u32x4 v = *(const u32x4*)p;
-#pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    out[2 * w] = __uint_as_float(v[w] << 16);
-    out[2 * w + 1] = __uint_as_float(v[w] & 0xFFFF0000u);
-  }
-}
-RGD_DEV void load8(const float* p, float* out) {
-  const float4 a = *(const float4*)p, b = *(const float4*)(p + 4);
-  out[0] = a.x; out[1] = a.y; out[2] = a.z; out[3] = a.w;
-  out[4] = b.x; out[5] = b.y; out[6] = b.z; out[7] = b.w;
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void attn_tail_combine_kernel(AttnArgs a, T* out) {
+// (row, KV head) attends the row's own tail in blocks of kChunk positions, then
+// merges the prefix-split partials of its heads with it in log-sum-exp form, in
+// a fixed order.
+template <int D>
+__global__ __launch_bounds__(256) void attn_tail_combine_kernel(AttnArgs a, float* out) {
+  constexpr int PARTS = 256 / D, kPre = 16;
   const int r = blockIdx.x, g = blockIdx.y;
-  const int D = a.D, G = a.Hq / a.Hkv;
+  const int G = a.Hq / a.Hkv, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const long long R = a.rows.R;
-  __shared__ __attribute__((aligned(16))) float qs[8][256];
-  __shared__ float sc[8][kTailBlk];
-  __shared__ float red[4];
-  __shared__ float accx[2048];  // [part][head][dim], part * D == 256
-  for (int i = threadIdx.x; i < G * D; i += 256)
-    qs[i / D][i % D] = load_f((const T*)a.q + ((long long)r * a.Hq + g * G) * D + i) * rsqrtf(float(D));
-  // the prefix-split partials do not depend on the tail: request them now so
-  // their latency overlaps the tail attention (first 16 splits, 2 pairs/thread)
-  constexpr int kPre = 16;
-  const int S = a.splits;
+  __shared__ __attribute__((aligned(16))) float qs[8][D];
+  __shared__ float sc[8][kChunk];
+  __shared__ float accx[PARTS][8][D];
+  __shared__ float al[8], wts[8][kMaxSplits + 1];  // merge weights; column `splits` is the tail
+  const int S = a.splits, n_all = a.tail_len;
+  for (int i = tid; i < G * D; i += 256)
+    qs[i / D][i % D] = ((const float*)a.q)[((long long)r * a.Hq + g * G) * D + i] * rsqrtf(float(D));
+  // the prefix-split partials do not depend on the tail: request them now (first
+  // 16 splits, 2 (head, dim) pairs per thread), from clamped addresses
   const long long pstep = R * a.Hq * D;
+  const float* po = a.part_o + ((long long)r * a.Hq + g * G) * D;
   float pre[2][kPre];
 #pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const int i = threadIdx.x + k * 256;
-    const int h = i / D, dd = i % D;
-    const float* po = a.part_o + ((long long)r * a.Hq + g * G + h) * D + dd;
+  for (int k = 0; k < 2; ++k)
 #pragma unroll
-    for (int sp = 0; sp < kPre; ++sp) pre[k][sp] = (i < G * D && sp < S) ? po[sp * pstep] : 0.f;
-  }
-  __syncthreads();
+    for (int sp = 0; sp < kPre; ++sp) pre[k][sp] = po[min(tid + k * 256, G * D - 1) + min(sp, S - 1) * pstep];
 
-  // tail attention, online softmax over blocks of 256 positions
   const int ps = a.kv.page_size;
   const int* pages = a.rows.pages ? a.rows.pages + (long long)r * a.rows.max_pages : nullptr;
-  const long long pstride = (long long)a.Hkv * D;
-  // weighted sum layout: thread = (part, d); part handles 8-position blocks
-  const int nparts = 256 / D;
-  const int d = threadIdx.x % D, part = threadIdx.x / D;
-  float mh[8], lh[8], acc[8];
-#pragma unroll
-  for (int h = 0; h < 8; ++h) {
-    mh[h] = -INFINITY;
-    lh[h] = 0.f;
-    acc[h] = 0.f;
-  }
-  for (int c0 = 0; c0 < a.tail_len; c0 += kTailBlk) {
-    const int n = min(kTailBlk, a.tail_len - c0);
-    const int j = threadIdx.x;
-    float dot[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    if (j < n) {
-      const int pos = c0 + j;
-      const T* kr = (const T*)a.kv.pool_k + (((long long)pages[pos / ps] * a.Hkv + g) * ps + pos % ps) * D;
-      for (int e0 = 0; e0 < D; e0 += 8) {
-        float kv[8];
-        load8(kr + e0, kv);
-#pragma unroll
-        for (int h = 0; h < 8; ++h) {
-          if (h < G) {
-            const float4 q0 = *(const float4*)&qs[h][e0], q1 = *(const float4*)&qs[h][e0 + 4];
-            dot[h] += q0.x * kv[0] + q0.y * kv[1] + q0.z * kv[2] + q0.w * kv[3] + q1.x * kv[4] + q1.y * kv[5] +
-                      q1.z * kv[6] + q1.w * kv[7];
-          }
-        }
-      }
-    }
-#pragma unroll
-    for (int h = 0; h < 8; ++h)
-      if (h < G) sc[h][j] = j < n ? dot[h] : -INFINITY;
+  const int d = tid % D, part = tid / D;
+  auto k_at = [&](int pos) -> const float* {
+    return (const float*)a.kv.pool_k + (((long long)pages[pos / ps] * a.Hkv + g) * ps + pos % ps) * D;
+  };
+  // 8 positions from a multiple of 8 lie inside one page (pages hold a multiple of 8)
+  auto v_at = [&](int pos) -> const float* {
+    return (const float*)a.kv.pool_v + (((long long)pages[pos / ps] * a.Hkv + g) * D + d) * ps + pos % ps;
+  };
+  float m[2] = {-INFINITY, -INFINITY}, l[2] = {0.f, 0.f};  // heads wave and wave + 4
+  float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  for (int c0 = 0; c0 < n_all; c0 += kChunk) {
+    const int n = min(kChunk, n_all - c0);
+    float v[8];
+    load8(v_at(c0 + min(part * 8, (n - 1) & ~7)), v);
+    __syncthreads();  // q is there; the block before is done with sc
+    f32_scores<D>(qs, sc, n, G, 1.f, [&](int p) { return k_at(c0 + p); });
     __syncthreads();
-    float alpha[8];
 #pragma unroll
-    for (int h = 0; h < 8; ++h) {
-      if (h >= G) break;
-      const float cm = block_max(sc[h][j], red);
-      const float mnew = fmaxf(mh[h], cm);
-      const float e = sc[h][j] == -INFINITY ? 0.f : __expf(sc[h][j] - mnew);
-      __syncthreads();
-      sc[h][j] = e;
-      const float bs = block_sum(e, red);
-      alpha[h] = mh[h] == -INFINITY ? 0.f : __expf(mh[h] - mnew);
-      lh[h] = lh[h] * alpha[h] + bs;
-      mh[h] = mnew;
+    for (int k = 0; k < 2; ++k) {
+      const int h = wave + 4 * k;
+      if (h < G) {
+        float alpha;
+        f32_softmax(sc[h], n, m[k], l[k], alpha);
+        if (lane == 0) al[h] = alpha;
+      }
     }
     __syncthreads();
 #pragma unroll
     for (int h = 0; h < 8; ++h)
-      if (h < G) acc[h] *= alpha[h];
-    for (int b0 = part * 8; b0 < n; b0 += nparts * 8) {
-      const int pos = c0 + b0;  // 8 positions inside one page (pages hold a multiple of 8)
-      float v[8];
-      load8((const T*)a.kv.pool_v + (((long long)pages[pos / ps] * a.Hkv + g) * D + d) * ps + pos % ps, v);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float ve = b0 + e < n ? v[e] : 0.f;
-#pragma unroll
-        for (int h = 0; h < 8; ++h)
-          if (h < G) acc[h] += sc[h][b0 + e < n ? b0 + e : 0] * ve;
-      }
-    }
-    __syncthreads();
+      if (h < G) acc[h] *= al[h];
+    f32_weighted<PARTS>(sc, n, G, part, v, acc, [&](int p) { return v_at(c0 + p); });
   }
-  // tail outputs per (head, dim): sum of the position parts in fixed order
-  __shared__ float wts[8][kMaxSplits + 1];  // merge weights; column `splits` is the tail
-  __syncthreads();
 #pragma unroll
   for (int h = 0; h < 8; ++h)
-    if (h < G) accx[(part * 8 + h) * D + d] = acc[h];
-  // log-sum-exp of every prefix split of the G heads, loaded in parallel
-  for (int i = threadIdx.x; i < G * S; i += 256) {
-    const int h = i / S, sp = i % S;
-    wts[h][sp] = a.part_lse[(sp * R + r) * a.Hq + g * G + h];
+    if (h < G) accx[part][h][d] = acc[h];
+  // merge weights of heads wave and wave + 4: lane sp holds split sp
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int h = wave + 4 * k;
+    if (h >= G) continue;
+    const float ls = a.part_lse[(min(lane, S - 1) * R + r) * a.Hq + g * G + h];
+    const float lse = lane < S ? ls : -INFINITY;
+    const float lt = l[k] > 0.f ? m[k] + __logf(l[k]) : -INFINITY;
+    const float M = wave_max(fmaxf(lse, lt));
+    const float w = lse == -INFINITY ? 0.f : __expf(lse - M), wt = lt == -INFINITY ? 0.f : __expf(lt - M);
+    const float den = wave_sum(w) + wt, inv = den > 0.f ? 1.0f / den : 0.f;
+    if (lane < S) wts[h][lane] = w * inv;
+    if (lane == 0) wts[h][S] = l[k] > 0.f ? wt * inv / l[k] : 0.f;  // applied to the unnormalised tail sum
   }
   __syncthreads();
-  if (threadIdx.x < G) {
-    const int h = threadIdx.x;
-    const float lt = lh[h] > 0.f ? mh[h] + __logf(lh[h]) : -INFINITY;
-    float M = lt;
-    for (int sp = 0; sp < S; ++sp) M = fmaxf(M, wts[h][sp]);
-    float den = 0.f;
-    for (int sp = 0; sp < S; ++sp) {
-      const float w = wts[h][sp] == -INFINITY ? 0.f : __expf(wts[h][sp] - M);
-      wts[h][sp] = w;
-      den += w;
-    }
-    const float wt = lt == -INFINITY ? 0.f : __expf(lt - M);
-    den += wt;
-    const float inv = den > 0.f ? 1.0f / den : 0.f;
-    for (int sp = 0; sp < S; ++sp) wts[h][sp] *= inv;
-    wts[h][S] = lh[h] > 0.f ? wt * inv / lh[h] : 0.f;  // applied to the unnormalised tail sum
-  }
-  __syncthreads();
-  for (int k = 0; k * 256 < G * D; ++k) {
-    const int i = threadIdx.x + k * 256;
+#pragma unroll
+  for (int k = 0; k < (8 * D + 255) / 256; ++k) {
+    const int i = tid + k * 256;
     if (i >= G * D) break;
     const int h = i / D, dd = i % D;
-    const int head = g * G + h;
     float tail = 0.f;
-    for (int pp = 0; pp < nparts; ++pp) tail += accx[(pp * 8 + h) * D + dd];
+#pragma unroll
+    for (int p = 0; p < PARTS; ++p) tail += accx[p][h][dd];
     float o = wts[h][S] * tail;
     if (k < 2) {
 #pragma unroll
       for (int sp = 0; sp < kPre; ++sp)
         if (sp < S) o += wts[h][sp] * pre[k & 1][sp];
     }
-    const float* po = a.part_o + ((long long)r * a.Hq + head) * D + dd;
 #pragma unroll 4
-    for (int sp = k < 2 ? kPre : 0; sp < S; ++sp) o += wts[h][sp] * po[sp * pstep];
-    store_f(out + ((long long)r * a.Hq + head) * D + dd, o);
+    for (int sp = k < 2 ? kPre : 0; sp < S; ++sp) o += wts[h][sp] * po[i + sp * pstep];
+    out[((long long)r * a.Hq + g * G) * D + i] = o;
   }
 }
 
@@ -963,21 +962,35 @@ hipError_t attn_prefix_bf16(const AttnArgs& a, hipStream_t s) {
   return hipSuccess;
 }
 
-template <typename T>
-hipError_t attn_prefix_vec(const AttnArgs& a, hipStream_t s) {
-  if (a.D > 256 || a.Hq / a.Hkv > 8 || a.split_len > kChunk) return hipErrorInvalidValue;
-  if (a.splits <= 0) return hipSuccess;
-  hipLaunchKernelGGL((attn_vec_kernel<T, true>), dim3(a.splits, a.Hkv, a.rows.R), dim3(256), 0, s, a);
+// f<D>() for the head dimensions of fp32 models
+template <typename F>
+static hipError_t by_head_dim(int D, F f) {
+  switch (D) {
+    case 8: f(std::integral_constant<int, 8>{}); break;
+    case 16: f(std::integral_constant<int, 16>{}); break;
+    case 32: f(std::integral_constant<int, 32>{}); break;
+    case 64: f(std::integral_constant<int, 64>{}); break;
+    case 128: f(std::integral_constant<int, 128>{}); break;
+    default: return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 
-template <typename T>
-hipError_t attn_tail_combine(const AttnArgs& a, T* out, hipStream_t s) {
-  if (a.D > 128 || a.D < 8 || 256 % a.D || a.Hq / a.Hkv > 8 || (a.tail_len > 0 && !a.rows.pages) ||
-      (a.tail_len > 0 && a.kv.page_size % 8) || a.splits > kMaxSplits)
+hipError_t attn_prefix_f32(const AttnArgs& a, hipStream_t s) {
+  if (a.Hq / a.Hkv > 8 || a.split_len > kChunk || a.split_len % 64) return hipErrorInvalidValue;
+  if (a.splits <= 0) return hipSuccess;
+  return by_head_dim(a.D, [&](auto d) {
+    hipLaunchKernelGGL(attn_prefix_f32_kernel<decltype(d)::value>, dim3(a.splits, a.Hkv, a.rows.R), dim3(256), 0, s, a);
+  });
+}
+
+hipError_t attn_tail_combine_f32(const AttnArgs& a, float* out, hipStream_t s) {
+  if (a.Hq / a.Hkv > 8 || (a.tail_len > 0 && !a.rows.pages) || (a.tail_len > 0 && a.kv.page_size % 8) || a.splits < 1 ||
+      a.splits > kMaxSplits)
     return hipErrorInvalidValue;
-  hipLaunchKernelGGL(attn_tail_combine_kernel<T>, dim3(a.rows.R, a.Hkv), dim3(256), 0, s, a, out);
-  return hipGetLastError();
+  return by_head_dim(a.D, [&](auto d) {
+    hipLaunchKernelGGL(attn_tail_combine_kernel<decltype(d)::value>, dim3(a.rows.R, a.Hkv), dim3(256), 0, s, a, out);
+  });
 }
 
 hipError_t attn_tail_merge_bf16(const AttnArgs& a, bf16_t* out, hipStream_t s) {
@@ -987,9 +1000,5 @@ hipError_t attn_tail_merge_bf16(const AttnArgs& a, bf16_t* out, hipStream_t s) {
   hipLaunchKernelGGL(attn_tail_merge_kernel, dim3(a.rows.R, a.Hkv), dim3(256), 0, s, a, out);
   return hipGetLastError();
 }
-
-template hipError_t attn_prefix_vec<float>(const AttnArgs&, hipStream_t);
-template hipError_t attn_prefix_vec<bf16_t>(const AttnArgs&, hipStream_t);
-template hipError_t attn_tail_combine<float>(const AttnArgs&, float*, hipStream_t);
 
 }  // namespace rgd

@@ -155,10 +155,10 @@ hipError_t attn_prefix_bf16(const AttnArgs& a, hipStream_t s);
 // bf16, head_dim 128, G <= 16: each row's paged tail on MFMA, merged with the
 // prefix-split partials into the final output
 hipError_t attn_tail_merge_bf16(const AttnArgs& a, bf16_t* out, hipStream_t s);
-template <typename T> hipError_t attn_prefix_vec(const AttnArgs& a, hipStream_t s);
-// fp32: attends each row's tail (vector units) and merges it with the
-// prefix-split partials 0 .. splits-1 into the final output
-template <typename T> hipError_t attn_tail_combine(const AttnArgs& a, T* out, hipStream_t s);
+// fp32: prefix-split partials, then each row's tail merged with them into the
+// final output (vector units; pages of a multiple of 8 positions)
+hipError_t attn_prefix_f32(const AttnArgs& a, hipStream_t s);
+hipError_t attn_tail_combine_f32(const AttnArgs& a, float* out, hipStream_t s);
 
 // ---------------------------------------------------------------- sampler ----
 hipError_t fill_u32(uint32_t* p, uint32_t v, long long n, hipStream_t s);

@@ -393,8 +393,8 @@ int run_attention(rgd_model* m, const KVLayout& kvl, const Rows& rows, const Hos
     }
     HIP_OK(attn_tail_merge_bf16(a, (bf16_t*)out, s));
   } else {
-    HIP_OK(attn_prefix_vec<float>(a, s));
-    HIP_OK(attn_tail_combine<float>(a, (float*)out, s));
+    HIP_OK(attn_prefix_f32(a, s));
+    HIP_OK(attn_tail_combine_f32(a, (float*)out, s));
   }
   return RGD_OK;
 }

@@ -10,6 +10,7 @@ import pytest
 import synth
 from oracle.model import Decoder, KVCache
 from tests.gpu_common import rel_err, torch
+from tests.test_gpu_kernels import _attn_case, _model
 
 pytestmark = pytest.mark.gpu
 
@@ -53,3 +54,15 @@ def test_prefill_and_decode_f32(rgd, shape, prompts, n):
         for s in range(1, steps):
             ref = dec.decode(int(forced[b, s - 1]), cache, tail)
             assert rel_err(got[s, b], np.asarray(ref)).max() <= 1e-5, (b, s)
+
+
+# head_dim, heads, kv heads: every head size, one and eight heads per KV head
+@pytest.mark.parametrize("D,hq,hk", [(8, 8, 1), (16, 3, 3), (32, 6, 2), (64, 8, 1), (128, 16, 2)])
+def test_attention_f32_heads(rgd, D, hq, hk):
+    """Splits of 256 positions with rows that end in and before them, V blocks past the row's end, tails of more than one block."""
+    w = synth.scaled(BASE, head_dim=D, n_heads=hq, n_kv_heads=hk, d_model=64, ffn=64, vocab=64)
+    m = _model(rgd, w, max_rows=64, max_pos=2048)
+    for P, tail, plens in [(1, 0, None), (257, 1, [1, 64, 255, 256, 257, 9]), (700, 257, [700, 513, 3, 700, 12, 256]),
+                           (70, 600, None)]:
+        err = _attn_case(rgd, w, m, 3, 2, P, tail, plens=plens, seed=P + tail)
+        assert err.max() <= 1e-5, (P, tail, err.max())
