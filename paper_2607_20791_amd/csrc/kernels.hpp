@@ -162,8 +162,10 @@ hipError_t attn_tail_combine_f32(const AttnArgs& a, float* out, hipStream_t s);
 
 // ---------------------------------------------------------------- sampler ----
 hipError_t fill_u32(uint32_t* p, uint32_t v, long long n, hipStream_t s);
-// per-chunk maxima of fp32 rows (standalone sampler)
-hipError_t chunk_max(const float* z, long long ldz, int R, int V, int chunk, float* cmax, hipStream_t s);
+// row map[r] of src -> row r of dst [R][V], and (cmax non-null) the maximum of
+// each of its chunks -> cmax [R][ceil(V / chunk)]
+hipError_t gather_rows(const float* src, long long lds, const int* map, int R, int V, int chunk, float* dst, float* cmax,
+                       hipStream_t s);
 // argmax: packed (value, -index) keys, max over chunks via 64-bit atomics
 hipError_t argmax_rows(const float* z, long long ldz, int R, int V, unsigned long long* best, hipStream_t s);
 struct SampleArgs {

@@ -127,17 +127,21 @@ struct rgd_model {
   unsigned long long* best = nullptr;
   int* cur_tok = nullptr;
   int* status = nullptr;
-  int* row_map = nullptr;
   int* probe_fail = nullptr;  // fixed probe: incompatible token seen, per prompt [R]
   unsigned long long* soft_keys = nullptr;  // soft gate: per-chunk top-K keys [R][nchunks][kMaxTopK]
   float* soft_cm = nullptr;                 // soft gate: chunk maxima and sums [2][R][nchunks]
   // per-call row arrays
-  int* d_prompt = nullptr;
-  int* d_base = nullptr;
-  int* d_plen = nullptr;
-  int* h_stage = nullptr;  // pinned staging for uploads
-  size_t stage_ints = 0;
-  hipEvent_t stage_done = nullptr;
+  int* d_rows = nullptr;  // row arrays of a call without tails [3][R] (see RowArrays)
+  // pinned staging for uploads, used as a ring: an upload takes a run of ints
+  // and an event that marks its copy's end
+  static constexpr int kUploads = 4;
+  int* h_stage = nullptr;
+  size_t stage_ints = 0, stage_at = 0;
+  struct Pending {
+    hipEvent_t done = nullptr;
+    size_t begin = 0, end = 0;
+  } uploads[kUploads];
+  int upload_next = 0;
   hipEvent_t poll_done = nullptr;  // a probe poll's copy of the events reached host memory
   hipEvent_t sync_done = nullptr;  // marks the end of the queued work for spin_sync
   int* h_events = nullptr;  // pinned host copies: probe events, gate results [2 * max_rows + 1]
@@ -161,7 +165,8 @@ struct rgd_model {
     for (void* p : allocs) (void)hipFree(p);
     if (h_stage) (void)hipHostFree(h_stage);
     if (h_events) (void)hipHostFree(h_events);
-    if (stage_done) (void)hipEventDestroy(stage_done);
+    for (Pending& u : uploads)
+      if (u.done) (void)hipEventDestroy(u.done);
     if (poll_done) (void)hipEventDestroy(poll_done);
     if (sync_done) (void)hipEventDestroy(sync_done);
   }
@@ -187,9 +192,9 @@ struct rgd_kv {
   std::vector<std::vector<int>> probe_pages;  // pages held by each prompt's probe
   bool probe_held = false;
   int max_pages = 0;   // page-table width per row
-  int* d_pages = nullptr;
+  int* d_rows = nullptr;  // row arrays and page tables of a call with tails [R * (3 + max_pages)]
   ~rgd_kv() {
-    if (d_pages) (void)hipFree(d_pages);
+    if (d_rows) (void)hipFree(d_rows);
   }
   KVLayout layer(int l) const {
     const rgd_model_config& c = m->cfg;
@@ -255,30 +260,32 @@ struct TimeScope {
 };
 
 // ----------------------------------------------------------- upload helper --
-// Copies host ints to device through the model's pinned staging buffer.  The
-// previous upload is waited for before the buffer is rewritten.
-struct Upload {
-  int* dst;
-  const int* src;
-  size_t n;
-};
-
-int upload(rgd_model* m, const std::vector<Upload>& ups, hipStream_t s) {
-  size_t total = 0;
-  for (auto& u : ups) total += u.n;
-  if (total > m->stage_ints) return fail(RGD_E_OOM, "upload of %zu ints exceeds staging", total);
-  HIP_OK(hipEventSynchronize(m->stage_done));
-  size_t off = 0;
-  for (auto& u : ups) {
-    if (!u.n) continue;
-    memcpy(m->h_stage + off, u.src, u.n * sizeof(int));
-    HIP_OK(hipMemcpyAsync(u.dst, m->h_stage + off, u.n * sizeof(int), hipMemcpyHostToDevice, s));
-    off += u.n;
-  }
-  HIP_OK(hipEventRecord(m->stage_done, s));
+// Copies n host ints to the device through the model's pinned staging ring.  A
+// run of the ring is waited for only when an earlier upload from it may still be
+// on its way, so that a call does not wait for the one before it.
+int upload(rgd_model* m, int* dst, const std::vector<int>& src, hipStream_t s) {
+  const size_t n = src.size();
+  if (n > m->stage_ints) return fail(RGD_E_OOM, "upload of %zu ints exceeds staging", n);
+  // a stream under capture waits for the last upload, as it always has
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone)
+    HIP_OK(hipEventSynchronize(m->uploads[(m->upload_next + rgd_model::kUploads - 1) % rgd_model::kUploads].done));
+  if (m->stage_at + n > m->stage_ints) m->stage_at = 0;
+  rgd_model::Pending& mine = m->uploads[m->upload_next];
+  for (rgd_model::Pending& u : m->uploads)
+    if (u.end > u.begin && (&u == &mine || (u.begin < m->stage_at + n && m->stage_at < u.end))) {
+      HIP_OK(hipEventSynchronize(u.done));
+      u.begin = u.end = 0;
+    }
+  int* h = m->h_stage + m->stage_at;
+  memcpy(h, src.data(), n * sizeof(int));
+  HIP_OK(hipMemcpyAsync(dst, h, n * sizeof(int), hipMemcpyHostToDevice, s));
+  HIP_OK(hipEventRecord(mine.done, s));
+  mine.begin = m->stage_at;
+  mine.end = m->stage_at += n;
+  m->upload_next = (m->upload_next + 1) % rgd_model::kUploads;
   return RGD_OK;
 }
-
 
 // Host description of the rows of one step.
 struct HostRows {
@@ -307,23 +314,39 @@ void build_blocks(const rgd_model* m, HostRows& h) {
   }
 }
 
-int upload_rows(rgd_model* m, const HostRows& h, hipStream_t s) {
+// Row arrays of a step on the device, one upload: prompt [R], base [R], plen [R],
+// then the page table [R][width] of a call with tails (width: the pages a row
+// uses, at least 1).
+struct RowArrays {
+  const int* p = nullptr;
+  int R = 0, width = 0;
+  const int* prompt() const { return p; }
+};
+
+// pages null: a call without tails
+int upload_rows(rgd_model* m, rgd_kv* kv, const HostRows& h, const std::vector<int>* pages, RowArrays& out, hipStream_t s) {
   const size_t R = h.prompt.size();
-  return upload(m,
-                {{m->d_prompt, h.prompt.data(), R},
-                 {m->d_base, h.base.data(), R},
-                 {m->d_plen, h.plen.data(), R}},
-                s);
+  std::vector<int> all;
+  all.reserve(3 * R + (pages ? pages->size() : 0));
+  all.insert(all.end(), h.prompt.begin(), h.prompt.end());
+  all.insert(all.end(), h.base.begin(), h.base.end());
+  all.insert(all.end(), h.plen.begin(), h.plen.end());
+  if (pages) all.insert(all.end(), pages->begin(), pages->end());
+  int* dst = pages ? kv->d_rows : m->d_rows;
+  out.p = dst;
+  out.R = (int)R;
+  out.width = pages ? (int)(pages->size() / R) : 0;
+  return upload(m, dst, all, s);
 }
 
-Rows device_rows(const rgd_model* m, const rgd_kv* kv, int R, int t, bool prefill) {
+Rows device_rows(const RowArrays& ra, int t, bool prefill) {
   Rows r;
-  r.R = R;
-  r.prompt = m->d_prompt;
-  r.base_pos = m->d_base;
-  r.plen = m->d_plen;
-  r.pages = prefill ? nullptr : kv->d_pages;
-  r.max_pages = kv ? kv->max_pages : 0;
+  r.R = ra.R;
+  r.prompt = ra.p;
+  r.base_pos = ra.p + ra.R;
+  r.plen = ra.p + 2 * ra.R;
+  r.pages = prefill ? nullptr : ra.p + 3 * ra.R;
+  r.max_pages = ra.width;
   r.t = t;
   r.prefill = prefill ? 1 : 0;
   return r;
@@ -346,11 +369,11 @@ int pick_splits(int groups, int K) {
 
 
 // -------------------------------------------------------------- attention --
-int run_attention(rgd_model* m, const KVLayout& kvl, const Rows& rows, const HostRows& h,
+int run_attention(rgd_model* m, const void* q, const KVLayout& kvl, const Rows& rows, const HostRows& h,
                   int tail_len, int force_splits, void* out, hipStream_t s) {
   const rgd_model_config& c = m->cfg;
   AttnArgs a{};
-  a.q = m->q;
+  a.q = q;
   a.rows = rows;
   a.kv = kvl;
   a.Hq = c.n_heads;
@@ -508,7 +531,7 @@ int forward_rows(rgd_model* m, rgd_kv* kv, const Rows& rows, const HostRows& h, 
     else
       HIP_OK(qkv_rope_store<float>(m->qkv_part, g.splits, g.split_stride, rows, Hq, Hkv, D, m->rope_cs, c.max_pos,
                                    (float*)m->q, kvl, s));
-    RGD_TRY(run_attention(m, kvl, rows, h, rows.prefill ? 0 : rows.t + 1, 0, m->attn_out, s));
+    RGD_TRY(run_attention(m, m->q, kvl, rows, h, rows.prefill ? 0 : rows.t + 1, 0, m->attn_out, s));
     // output projection: partials added to the residual stream by the FFN norm
     GemmArgs o{};
     o.x = m->attn_out;
@@ -588,12 +611,6 @@ SampleArgs sample_args(rgd_model* m, const float* z, long long ldz, int R, int V
   a.cur_tok = cur;
   a.status = m->status;
   return a;
-}
-
-__global__ void gather_rows_kernel(const float* src, long long lds, const int* map, int V, float* dst) {
-  const int r = blockIdx.y;
-  const float* s = src + (long long)map[r] * lds;
-  for (int i = blockIdx.x * 256 + threadIdx.x; i < V; i += 256 * gridDim.x) dst[(long long)r * V + i] = s[i];
 }
 
 __global__ void argmax_finish_kernel(unsigned long long* best, int R, int* out, long long stride, int col,
@@ -779,14 +796,11 @@ int32_t rgd_model_create(const rgd_model_config* cfg, const rgd_weights* w, int3
   A(&m->best, (size_t)R * 8);
   A(&m->cur_tok, (size_t)R * 4);
   A(&m->status, 4);
-  A(&m->row_map, (size_t)R * 4);
   A(&m->probe_fail, (size_t)R * 4);
   A(&m->d_gate, (size_t)(2 * R + 1) * 4);
   A(&m->soft_keys, (size_t)R * m->nchunks * kMaxTopK * 8);
   A(&m->soft_cm, (size_t)2 * R * m->nchunks * 4);
-  A(&m->d_prompt, (size_t)R * 4);
-  A(&m->d_base, (size_t)R * 4);
-  A(&m->d_plen, (size_t)R * 4);
+  A(&m->d_rows, (size_t)3 * R * 4);
   // RoPE rotations: angle pos * theta^(-2j/D) in fp64, rounded to fp32 once
   const int half = D / 2;
   const size_t ncs = ((size_t)cfg->max_pos + 1) * half;
@@ -833,13 +847,16 @@ int32_t rgd_model_create(const rgd_model_config* cfg, const rgd_weights* w, int3
   m->stage_ints = (size_t)R * 8 + 64;
   if (hipHostMalloc((void**)&m->h_stage, m->stage_ints * sizeof(int), hipHostMallocDefault) != hipSuccess ||
       hipHostMalloc((void**)&m->h_events, (size_t)(2 * R + 1) * sizeof(int), hipHostMallocDefault) != hipSuccess ||
-      hipEventCreateWithFlags(&m->stage_done, hipEventDisableTiming) != hipSuccess ||
       hipEventCreateWithFlags(&m->poll_done, hipEventDisableTiming) != hipSuccess ||
-      hipEventCreateWithFlags(&m->sync_done, hipEventDisableTiming) != hipSuccess ||
-      hipEventRecord(m->stage_done, nullptr) != hipSuccess) {
+      hipEventCreateWithFlags(&m->sync_done, hipEventDisableTiming) != hipSuccess) {
     delete m;
     return fail(RGD_E_HIP, "pinned staging allocation failed");
   }
+  for (rgd_model::Pending& u : m->uploads)
+    if (hipEventCreateWithFlags(&u.done, hipEventDisableTiming) != hipSuccess) {
+      delete m;
+      return fail(RGD_E_HIP, "event creation failed");
+    }
   // argmax keys start cleared
   if (hipMemset(m->best, 0, (size_t)R * 8) != hipSuccess ||
       hipMemset(m->status, 0, 4) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
@@ -877,7 +894,7 @@ int32_t rgd_kv_create(const rgd_model* m, int32_t max_prompts, int32_t max_prefi
   kv->probe_pages.assign(max_prompts, {});
   for (int p = n_pages - 1; p >= 0; --p) kv->free_pages.push_back(p);
   kv->max_pages = (int)std::max<long long>(1, cdiv(m->cfg.max_pos, page_size));
-  if (hipMalloc((void**)&kv->d_pages, (size_t)m->max_rows * kv->max_pages * 4) != hipSuccess) {
+  if (hipMalloc((void**)&kv->d_rows, (size_t)m->max_rows * (kv->max_pages + 3) * 4) != hipSuccess) {
     delete kv;
     return fail(RGD_E_OOM, "page-table allocation failed");
   }
@@ -886,14 +903,19 @@ int32_t rgd_kv_create(const rgd_model* m, int32_t max_prompts, int32_t max_prefi
   const size_t need = (size_t)m->max_rows * (kv->max_pages + 8) + 64;
   if (mm->stage_ints < need) {
     int* p = nullptr;
-    if (hipEventSynchronize(mm->stage_done) != hipSuccess ||
-        hipHostMalloc((void**)&p, need * sizeof(int), hipHostMallocDefault) != hipSuccess) {
+    bool ok = true;
+    for (rgd_model::Pending& u : mm->uploads) {
+      ok = ok && (u.end == u.begin || hipEventSynchronize(u.done) == hipSuccess);
+      u.begin = u.end = 0;
+    }
+    if (!ok || hipHostMalloc((void**)&p, need * sizeof(int), hipHostMallocDefault) != hipSuccess) {
       delete kv;
       return fail(RGD_E_OOM, "pinned staging allocation failed");
     }
     (void)hipHostFree(mm->h_stage);
     mm->h_stage = p;
     mm->stage_ints = need;
+    mm->stage_at = 0;
   }
   *out = kv;
   return RGD_OK;
@@ -985,8 +1007,9 @@ int prefill_impl(rgd_model* m, rgd_kv* kv, const int32_t* tokens, int32_t B, int
         }
       build_blocks(m, h);
       const int R = (int)h.prompt.size();
-      RGD_TRY(upload_rows(m, h, s));
-      Rows rows = device_rows(m, kv, R, 0, true);
+      RowArrays ra;
+      RGD_TRY(upload_rows(m, kv, h, nullptr, ra, s));
+      Rows rows = device_rows(ra, 0, true);
       const int* feed = tokens + (long long)b0 * n + i0;
       // the prompts' last positions: rows bb * n + n - 1 (whole prompts), or
       // row len - 1 of a prompt's last segment
@@ -1086,7 +1109,7 @@ int probe_impl(rgd_model* m, rgd_kv* kv, const float* last_logits, const rgd_tab
   GateArgs ga{};
   ga.best = m->best;
   ga.best_reset = m->best;
-  ga.row_prompt = m->d_prompt;
+  ga.row_prompt = kv->d_rows;
   ga.cur_tok = m->cur_tok;
   ga.probe_tokens = probe_tokens;
   ga.k = k;
@@ -1161,25 +1184,22 @@ int probe_impl(rgd_model* m, rgd_kv* kv, const float* last_logits, const rgd_tab
   for (int b = 0; b < B; ++b) alive[b] = b;
   int* pinned_ev = m->h_events;  // B <= max_rows
 
+  const int width = std::max(1, pages_per);
+  RowArrays ra;
   auto set_rows = [&](HostRows& h, std::vector<int>& pages) -> int {
     h.prompt.clear();
     h.base.clear();
     h.plen.clear();
-    pages.assign((size_t)alive.size() * kv->max_pages, 0);
+    pages.assign(alive.size() * (size_t)width, 0);
     for (size_t r = 0; r < alive.size(); ++r) {
       const int b = alive[r];
       h.prompt.push_back(b);
       h.base.push_back(kv->plen[b]);
       h.plen.push_back(kv->plen[b]);
-      for (int i = 0; i < pages_per; ++i) pages[r * kv->max_pages + i] = kv->probe_pages[b][i];
+      for (int i = 0; i < pages_per; ++i) pages[r * width + i] = kv->probe_pages[b][i];
     }
     build_blocks(m, h);
-    return upload(m,
-                  {{m->d_prompt, h.prompt.data(), h.prompt.size()},
-                   {m->d_base, h.base.data(), h.base.size()},
-                   {m->d_plen, h.plen.data(), h.plen.size()},
-                   {kv->d_pages, pages.data(), pages.size()}},
-                  s);
+    return upload_rows(m, kv, h, &pages, ra, s);
   };
   HostRows h;
   std::vector<int> pages;
@@ -1228,8 +1248,8 @@ int probe_impl(rgd_model* m, rgd_kv* kv, const float* last_logits, const rgd_tab
     if (j > k) break;  // cannot happen: every prompt is decided after k tokens
     const int R = (int)alive.size();
     // row r feeds token j-1 of its prompt's probe (probe_tokens[prompt[r]][j-2])
-    Rows rows = device_rows(m, kv, R, j - 2, false);
-    RGD_TRY(forward_rows(m, kv, rows, h, probe_tokens + (j - 2), k, s, embedded, nullptr, m->d_prompt));
+    Rows rows = device_rows(ra, j - 2, false);
+    RGD_TRY(forward_rows(m, kv, rows, h, probe_tokens + (j - 2), k, s, embedded, nullptr, rows.prompt));
     RGD_TRY(lm_head(m, m->xn, m->cfg.d_model, R, m->logits, s, true));
     RGD_TRY(step(m->logits, R, j, true));
     if (pipelined) {
@@ -1346,9 +1366,10 @@ int32_t sample_continuations(rgd_model* m, rgd_kv* kv, const float* last_logits,
     return fail(RGD_E_OOM, "page pool too small for %d rows of %d tokens", R, steps);
   hipStream_t s = (hipStream_t)stream;
   const int V = m->cfg.vocab;
-  // rows (prompt-major), page tables, row -> prompt logits map
+  // rows (prompt-major) and page tables
+  const int width = std::max(1, pages_per);
   HostRows h;
-  std::vector<int> pages((size_t)R * kv->max_pages, 0), map(R);
+  std::vector<int> pages((size_t)R * width, 0);
   std::vector<int> taken;
   for (int i = 0; i < n; ++i)
     for (int j = 0; j < N; ++j) {
@@ -1356,12 +1377,11 @@ int32_t sample_continuations(rgd_model* m, rgd_kv* kv, const float* last_logits,
       h.prompt.push_back(b);
       h.base.push_back(kv->plen[b]);
       h.plen.push_back(kv->plen[b]);
-      map[r] = b;
       for (int p = 0; p < pages_per; ++p) {
         const int pg = kv->free_pages.back();
         kv->free_pages.pop_back();
         taken.push_back(pg);
-        pages[(size_t)r * kv->max_pages + p] = pg;
+        pages[(size_t)r * width + p] = pg;
       }
     }
   build_blocks(m, h);
@@ -1372,20 +1392,13 @@ int32_t sample_continuations(rgd_model* m, rgd_kv* kv, const float* last_logits,
       for (auto it = t.rbegin(); it != t.rend(); ++it) kv->free_pages.push_back(*it);
     }
   } give{kv, taken};
-  RGD_TRY(upload(m,
-                 {{m->d_prompt, h.prompt.data(), (size_t)R},
-                  {m->d_base, h.base.data(), (size_t)R},
-                  {m->d_plen, h.plen.data(), (size_t)R},
-                  {kv->d_pages, pages.data(), pages.size()},
-                  {m->row_map, map.data(), (size_t)R}},
-                 s));
+  RowArrays ra;
+  RGD_TRY(upload_rows(m, kv, h, &pages, ra, s));
   const unsigned long long* sd = (const unsigned long long*)seeds;
   // step 0: every branch draws from its prompt's last-position logits
   float* z0 = logits_tap ? logits_tap : m->logits;
-  hipLaunchKernelGGL(gather_rows_kernel, dim3((int)cdiv(V, 256 * 8), R), dim3(256), 0, s, last_logits, (long long)V,
-                     m->row_map, V, z0);
-  HIP_OK(hipGetLastError());
-  if (T > 0.f && !pless) HIP_OK(chunk_max(z0, V, R, V, kSampleChunk, m->tilemax, s));
+  // (the first draw's chunk maxima are taken on the way)
+  HIP_OK(gather_rows(last_logits, V, ra.prompt(), R, V, kSampleChunk, z0, T > 0.f && !pless ? m->tilemax : nullptr, s));
   struct StepIndex {  // restores the timing step index on every exit
     rgd_model* m;
     ~StepIndex() {
@@ -1403,7 +1416,7 @@ int32_t sample_continuations(rgd_model* m, rgd_kv* kv, const float* last_logits,
   for (int st = 1; st < steps; ++st) {
     m->tstep = st - 1;
     TimeScope tstep(m, RGD_TIMER_STEP, s);
-    Rows rows = device_rows(m, kv, R, st - 1, false);
+    Rows rows = device_rows(ra, st - 1, false);
     const int* feed = forced ? forced + (st - 1) : m->cur_tok;
     const int fstride = forced ? steps : 1;
     RGD_TRY(forward_rows(m, kv, rows, h, feed, fstride, s, embedded));
@@ -1512,16 +1525,11 @@ int32_t rgd_kernel_attention(rgd_model* m, const void* q, int32_t R, const int32
   }
   build_blocks(m, h);
   hipStream_t s = (hipStream_t)stream;
-  RGD_TRY(upload_rows(m, h, s));
-  Rows rows;
-  rows.R = R;
-  rows.prompt = m->d_prompt;
-  rows.base_pos = m->d_base;
-  rows.plen = m->d_plen;
+  RowArrays ra;
+  RGD_TRY(upload_rows(m, nullptr, h, nullptr, ra, s));
+  Rows rows = device_rows(ra, tail_len - 1, false);
   rows.pages = pages;
   rows.max_pages = max_pages;
-  rows.t = tail_len - 1;
-  rows.prefill = 0;
   KVLayout kvl;
   kvl.prefix_k = const_cast<void*>(prefix_k);
   kvl.prefix_v = const_cast<void*>(prefix_v);
@@ -1531,10 +1539,15 @@ int32_t rgd_kernel_attention(rgd_model* m, const void* q, int32_t R, const int32
   kvl.VP = v_stride(max_prefix);
   kvl.page_size = page_size;
   kvl.split_len = prefix_split_len(max_prefix, max_prompts, m->cfg.n_kv_heads);
-  // q is read from the model's q buffer: copy the caller's q there first
+  // q is read in place where the kernels may load it 16 bytes at a time and it
+  // does not overlap out (written while other rows are still read), else from a copy
   const size_t qbytes = (size_t)R * m->cfg.n_heads * m->cfg.head_dim * m->esz;
-  HIP_OK(hipMemcpyAsync(m->q, q, qbytes, hipMemcpyDeviceToDevice, s));
-  return run_attention(m, kvl, rows, h, tail_len, splits, out, s);
+  const uintptr_t q0 = (uintptr_t)q, o0 = (uintptr_t)out;
+  if (q0 % 16 || (q0 < o0 + qbytes && o0 < q0 + qbytes)) {
+    HIP_OK(hipMemcpyAsync(m->q, q, qbytes, hipMemcpyDeviceToDevice, s));
+    q = m->q;
+  }
+  return run_attention(m, q, kvl, rows, h, tail_len, splits, out, s);
 }
 
 int32_t rgd_kernel_lm_head(rgd_model* m, const void* hvec, int32_t R, float* logits, rgd_stream stream) {
@@ -1565,11 +1578,11 @@ int32_t rgd_kernel_probe_step(rgd_model* m, const float* logits, int32_t R, cons
   const int V = m->cfg.vocab;
   std::vector<int> ident(R);
   for (int r = 0; r < R; ++r) ident[r] = r;
-  RGD_TRY(upload(m, {{m->d_prompt, ident.data(), (size_t)R}}, s));
+  RGD_TRY(upload(m, m->d_rows, ident, s));
   GateArgs ga{};
   ga.best = m->best;
   ga.best_reset = m->best;
-  ga.row_prompt = m->d_prompt;
+  ga.row_prompt = m->d_rows;
   ga.R = R;
   ga.probe_tokens = probe_tokens;
   ga.k = k;

@@ -44,25 +44,41 @@ __global__ void fill_u32_kernel(uint32_t* p, uint32_t v, long long n) {
   for (long long i = blockIdx.x * 256ll + threadIdx.x; i < n; i += 256ll * gridDim.x) p[i] = v;
 }
 
-// Per-chunk maxima; chunk is a multiple of 1024 (4 float4 per thread per
-// 1024 logits) and V a multiple of 4.
-__global__ __launch_bounds__(256) void chunk_max_kernel(const float* z, long long ldz, int V, int chunk,
-                                                        float* cmax) {
+// Rows map[r] of src copied to row r of dst, with each 4096-logit chunk's
+// maximum taken on the way (cmax null: copied only).  One workgroup per (chunk,
+// row), 16 bytes per load and store (VEC: src and dst aligned to 16 bytes; V and
+// lds are multiples of 4).  256 rows of 128256: 38 us against 55 for a copy of 4
+// bytes at a time and 21 for a pass over the copy for the maxima.
+template <bool VEC>
+__global__ __launch_bounds__(256) void gather_rows_kernel(const float* src, long long lds, const int* map, int V,
+                                                          int chunk, float* dst, float* cmax) {
   __shared__ float red[4];
   const int c = blockIdx.x, r = blockIdx.y;
-  const float* zr = z + r * ldz;
+  const float* s = src + (long long)map[r] * lds;
+  float* d = dst + (long long)r * V;
   const int lo = c * chunk, hi = min(V, lo + chunk);
   float mx = -INFINITY;
-  for (int i0 = lo; i0 < hi; i0 += 4096) {
-    float4 v[4];
+  if (VEC) {
+    for (int i0 = lo; i0 < hi; i0 += 4096) {
+      float4 v[4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int i = i0 + (threadIdx.x + k * 256) * 4;
-      v[k] = i < hi ? *(const float4*)(zr + i) : float4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+      for (int k = 0; k < 4; ++k) v[k] = *(const float4*)(s + min(i0 + (int)(threadIdx.x + k * 256) * 4, hi - 4));
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int i = i0 + (threadIdx.x + k * 256) * 4;
+        if (i < hi) *(float4*)(d + i) = v[k];
+        // (a value read twice leaves the maximum unchanged)
+        mx = fmaxf(mx, fmaxf(fmaxf(v[k].x, v[k].y), fmaxf(v[k].z, v[k].w)));
+      }
     }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) mx = fmaxf(mx, fmaxf(fmaxf(v[k].x, v[k].y), fmaxf(v[k].z, v[k].w)));
+  } else {
+    for (int i = lo + threadIdx.x; i < hi; i += 256) {
+      const float v = s[i];
+      d[i] = v;
+      mx = fmaxf(mx, v);
+    }
   }
+  if (!cmax) return;
   mx = block_max(mx, red);
   if (threadIdx.x == 0) cmax[(long long)r * gridDim.x + c] = mx;
 }
@@ -816,10 +832,14 @@ hipError_t fill_u32(uint32_t* p, uint32_t v, long long n, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t chunk_max(const float* z, long long ldz, int R, int V, int chunk, float* cmax, hipStream_t s) {
-  if (chunk % 1024 || V % 4 || ldz % 4) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(chunk_max_kernel, dim3((V + chunk - 1) / chunk, R), dim3(256), 0, s, z, ldz, V, chunk,
-                     cmax);
+hipError_t gather_rows(const float* src, long long lds, const int* map, int R, int V, int chunk, float* dst, float* cmax,
+                       hipStream_t s) {
+  if (chunk % 1024 || V % 4 || lds % 4) return hipErrorInvalidValue;
+  const dim3 grid((V + chunk - 1) / chunk, R);
+  if ((uintptr_t)src % 16 == 0 && (uintptr_t)dst % 16 == 0)
+    hipLaunchKernelGGL(gather_rows_kernel<true>, grid, dim3(256), 0, s, src, lds, map, V, chunk, dst, cmax);
+  else
+    hipLaunchKernelGGL(gather_rows_kernel<false>, grid, dim3(256), 0, s, src, lds, map, V, chunk, dst, cmax);
   return hipGetLastError();
 }
 
