@@ -56,6 +56,22 @@ constexpr float kNoRef = -3.0e38f;
 #define RGD_ATTN_RING 5
 #endif
 
+// The partials of a row's prefix splits are combined one after the other, in
+// split order: with (mx, den) the running maximum of their log-sum-exps and the
+// sum of their weights relative to it, the outputs summed so far are scaled by a
+// and the next split's normalised output enters with weight b.  The kernel that
+// walks over all splits and the merge kernel share this step (and round a
+// split's output to bf16 before it), so both give the same bits.
+RGD_DEV void merge_step(float& mx, float& den, float lse, float& a, float& b) {
+  const float nm = fmaxf(mx, lse);
+  a = mx == -INFINITY ? 0.f : __expf(mx - nm);
+  b = __expf(lse - nm);
+  den = fmaf(den, a, b);
+  mx = nm;
+}
+RGD_DEV float merge_value(float o, float a, float b, float part) { return fmaf(b, part, o * a); }
+RGD_DEV float merge_lse(float mx, float den) { return den > 0.f ? mx + __logf(den) : -INFINITY; }
+
 // K tiles sit in LDS as unpadded 256-byte rows whose 16-byte chunks are
 // XOR-swizzled: chunk c of row r is stored at chunk c ^ kswz(r).  A fragment
 // read touches rows {0..3, 8..11, 16..19, 24..27} (+ a multiple of 4) of a
@@ -89,16 +105,25 @@ RGD_DEV int k_gather_row(int h, int e, int l16) { return h * 32 + (l16 >> 2) * 8
 // registers one tile ahead and stored into a ring of three LDS buffers, and
 // the scores of tile t+1 are computed (MFMA) while the softmax of tile t runs
 // on the vector units.  One barrier per tile.
-template <int NW, int NQ>
-__global__ __launch_bounds__(NW * 64) void attn_prefix_kernel(AttnArgs a) {
+//
+// WALK: one workgroup per (KV head, row block) walks over all splits, closes
+// each at its end as a separate workgroup would and merges it into a second set of
+// accumulators.  Rows whose prefix ends with the walk are written out, those with
+// positions left for the tail kernel leave their merged partial (fp32) and its
+// log-sum-exp as partial 0.  2048 rows, 32 heads, 4096 positions, first / second
+// half: 67 / 205 us, against 155 / 310 split and 115 / 140 for the merge of the
+// partials (four waves of twice the query vectors 90 / 250: one wave per SIMD
+// hides too little).
+template <int NW, int NQ, bool WALK>
+__global__ __launch_bounds__(NW * 64) void attn_prefix_kernel(AttnArgs a, bf16_t* out) {
   constexpr int D = 128, TP = 64, NT = NW * 64, NB = 3;
   static_assert(NW * NQ * 16 == RGD_ATTN_QV, "a workgroup covers RGD_ATTN_QV query vectors");
-  const int s = blockIdx.x, g = blockIdx.y;
-  // the row block comes with the arguments
-  const int4 rb = a.rblk[blockIdx.z];
+  const int s = WALK ? 0 : blockIdx.x, g = blockIdx.y;
+  // the row block comes with the arguments (walks: the last, longest ones first)
+  const int4 rb = a.rblk[WALK ? gridDim.z - 1 - blockIdx.z : blockIdx.z];
   const int r0 = rb.x, nr = rb.y, b = rb.z, maxplen = rb.w;
   const int lo = s * a.split_len;
-  const int hi = min(lo + a.split_len, maxplen);
+  const int hi = WALK ? maxplen : min(lo + a.split_len, maxplen);
   const int G = a.Hq / a.Hkv;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int l16 = lane & 15, grp = lane >> 4;
@@ -157,6 +182,16 @@ __global__ __launch_bounds__(NW * 64) void attn_prefix_kernel(AttnArgs a) {
     lacc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int dt = 0; dt < 8; ++dt) o[dt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  // WALK: the splits merged so far
+  float wmx[NQ], wden[NQ];
+  f32x4 wo[WALK ? 8 : 1][NQ];
+#pragma unroll
+  for (int nt = 0; nt < NQ; ++nt) {
+    wmx[nt] = -INFINITY;
+    wden[nt] = 0.f;
+#pragma unroll
+    for (int dt = 0; dt < (WALK ? 8 : 1); ++dt) wo[dt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
   const u32x4 ones = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};  // bf16 1.0 x 8
 
@@ -361,10 +396,37 @@ __global__ __launch_bounds__(NW * 64) void attn_prefix_kernel(AttnArgs a) {
     }
   };
 
+  // WALK: ends the split of the tile just done
+  auto close_split = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int nt = 0; nt < NQ; ++nt) {
+      const float lt = lacc[nt][0];
+      const bool some = lt > 0.f;
+      const float inv = some ? 1.0f / lt : 0.f;
+      float wa = 1.f, wb = 0.f;
+      if (some) merge_step(wmx[nt], wden[nt], (m[nt] + __log2f(lt)) * kLn2, wa, wb);
+#pragma unroll
+      for (int dt = 0; dt < (WALK ? 8 : 1); ++dt) {
+#pragma unroll
+        for (int w = 0; w < 2; ++w) {
+          const uint32_t p = pack2(o[dt][nt][2 * w] * inv, o[dt][nt][2 * w + 1] * inv);
+          const float p0 = __uint_as_float(p << 16), p1 = __uint_as_float(p & 0xFFFF0000u);
+          if (some) {
+            wo[dt][nt][2 * w] = merge_value(wo[dt][nt][2 * w], wa, wb, p0);
+            wo[dt][nt][2 * w + 1] = merge_value(wo[dt][nt][2 * w + 1], wa, wb, p1);
+          }
+        }
+        o[dt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+      m[nt] = kNoRef;
+      lacc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+  };
   const int ntile = hi > lo ? (hi - lo + TP - 1) / TP : 0;
   // The loop is reached only through the prologue, whose first store waits for
   // every earlier load (the Q fragments included), so no wait for them is
   // needed inside the loop.
+  const int tiles_split = a.split_len / TP;
   if (ntile > 0) {
     load_tile(lo);
     store_tile(0);
@@ -391,6 +453,7 @@ __global__ __launch_bounds__(NW * 64) void attn_prefix_kernel(AttnArgs a) {
         prime(nb, 0, cb, 1, ring);
         prepare(t0 + 32, sb);
         stream(nb, 0, cb, 1, sb, sa, ring);
+        if (WALK && ((t + 1) % tiles_split == 0 || t + 1 == ntile)) close_split();  // uniform
       }
     };
     static_assert(NB == 3, "the tile loop is unrolled by the number of LDS tile buffers");
@@ -401,6 +464,23 @@ __global__ __launch_bounds__(NW * 64) void attn_prefix_kernel(AttnArgs a) {
     }
   }
 
+  if (WALK) {
+#pragma unroll
+    for (int nt = 0; nt < NQ; ++nt) {
+      if (!vok[nt]) continue;
+      const long long idx = (long long)vrow[nt] * a.Hq + vhead[nt];
+      const float inv = wden[nt] > 0.f ? 1.0f / wden[nt] : 0.f;
+      const bool done = prefix_part_end(pl[nt], a.split_len) == pl[nt];
+#pragma unroll
+      for (int dt = 0; dt < (WALK ? 8 : 1); ++dt) {
+        const f32x4 y = wo[dt][nt] * inv;
+        if (done) *(u32x2*)(out + idx * D + dt * 16 + grp * 4) = u32x2{pack2(y[0], y[1]), pack2(y[2], y[3])};
+        else *(f32x4*)(a.part_o + idx * D + dt * 16 + grp * 4) = y;
+      }
+      if (!done && grp == 0) a.part_lse[idx] = merge_lse(wmx[nt], wden[nt]);
+    }
+    return;
+  }
 #pragma unroll
   for (int nt = 0; nt < NQ; ++nt) {
     const float lt = lacc[nt][0];
@@ -669,14 +749,16 @@ __global__ __launch_bounds__(256) void attn_tail_combine_kernel(AttnArgs a, floa
 // the pages (K rows in the gathered order of the prefix kernel, so every lane
 // ends up with eight consecutive positions).  The four waves' tail states are
 // merged through LDS, and wave h writes query head h's output.  The merge is
-// in log-sum-exp form with a fixed split order; for the wave's first head the
-// prefix-split partials are combined into one while the wave's first tile is
-// loading, which leaves a two-term merge with the tail after the exchange.
+// in log-sum-exp form: a head's prefix-split partials are combined in split order
+// (for the wave's first head while its first tile is loading), which leaves a
+// two-term merge with the tail after the exchange.  WALKED: the splits come
+// combined, as one fp32 partial, and the rows are those of a list.
 constexpr int kMergeMaxSplits = 64;
 
-__global__ __launch_bounds__(256) void attn_tail_merge_kernel(AttnArgs a, bf16_t* out) {
+template <bool WALKED>
+__global__ __launch_bounds__(256) void attn_tail_merge_kernel(AttnArgs a, bf16_t* out, const int* rowlist) {
   constexpr int D = 128, TT = 32;
-  const int r = blockIdx.x, g = blockIdx.y;
+  const int r = WALKED ? rowlist[blockIdx.x] : blockIdx.x, g = blockIdx.y;
   const int G = a.Hq / a.Hkv;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int l16 = lane & 15, grp = lane >> 4;
@@ -711,15 +793,22 @@ __global__ __launch_bounds__(256) void attn_tail_merge_kernel(AttnArgs a, bf16_t
   // masked afterwards: a predicated load makes the compiler wait for it where
   // the branches join, one memory round trip each.)
   // (a wave past the G heads loads head G-1's and does not use them)
-  uint32_t pre[kPrefetch];  // bf16 pairs
+  uint32_t pre[WALKED ? 2 : kPrefetch];  // bf16 pairs (WALKED: the two fp32 values)
   float pre_lse;
   {
     const int head = g * G + min(wave, G - 1);
-    const bf16_t* po = (const bf16_t*)a.part_o + ((long long)r * a.Hq + head) * D + 2 * lane;
+    const long long i0 = ((long long)r * a.Hq + head) * D + 2 * lane;
+    if constexpr (WALKED) {
+      const u32x2 v = *(const u32x2*)(a.part_o + i0);
+      pre[0] = v[0];
+      pre[1] = v[1];
+      pre_lse = a.part_lse[(long long)r * a.Hq + head];
+    } else {
+      const bf16_t* po = (const bf16_t*)a.part_o + i0;
 #pragma unroll
-    for (int k = 0; k < kPrefetch; ++k) pre[k] = *(const uint32_t*)(po + min(k, S - 1) * pstep);
-    const float ls = a.part_lse[((long long)min(lane, S - 1) * R + r) * a.Hq + head];
-    pre_lse = lane < S ? ls : -INFINITY;
+      for (int k = 0; k < kPrefetch; ++k) pre[k] = *(const uint32_t*)(po + min(k, S - 1) * pstep);
+      pre_lse = a.part_lse[((long long)min(lane, S - 1) * R + r) * a.Hq + head];
+    }
   }
 
   u32x4 qf[4];
@@ -736,42 +825,44 @@ __global__ __launch_bounds__(256) void attn_tail_merge_kernel(AttnArgs a, bf16_t
   f32x4 o[8];
 #pragma unroll
   for (int dt = 0; dt < 8; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // The prefix splits of this wave's first head combined into one partial
-  // (natural-log log-sum-exp s_lse, normalised output s_o0 / s_o1 for dims
-  // 2*lane, 2*lane+1), in fixed split order.  It needs no tail data, so it is
-  // formed while the first tile's loads are in flight.
+  // The prefix splits of one head combined into one partial (log-sum-exp
+  // s_lse, normalised output s_o0 / s_o1 for dims 2*lane, 2*lane+1).  It needs no
+  // tail data: the first head's is formed while the first tile's loads are in
+  // flight.  Lane sp holds split sp's log-sum-exp.
   float s_lse = -INFINITY, s_o0 = 0.f, s_o1 = 0.f;
-  auto combine_splits = [&]() {
-    const int head = g * G + min(wave, G - 1);
-    float mx = pre_lse;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-    const float w = pre_lse == -INFINITY ? 0.f : __expf(pre_lse - mx);
-    float den = w;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) den += __shfl_xor(den, off, 64);
-    const float inv = den > 0.f ? 1.f / den : 0.f;
-    const bf16_t* po = (const bf16_t*)a.part_o + ((long long)r * a.Hq + head) * D + 2 * lane;
-    float o0 = 0.f, o1 = 0.f;
-    // weight of split sp sits in lane sp
-#pragma unroll
-    for (int k = 0; k < kPrefetch; ++k) {
-      if (k < S) {
-        const float wk = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), k)) * inv;
-        o0 += wk * __uint_as_float(pre[k] << 16);
-        o1 += wk * __uint_as_float(pre[k] & 0xFFFF0000u);
+  auto combine_splits = [&](int head, float lses, bool first) {
+    if constexpr (WALKED) {
+      s_lse = lses;
+      s_o0 = __uint_as_float(pre[0]);
+      s_o1 = __uint_as_float(pre[1]);
+      if (!first) {
+        const float* po = a.part_o + ((long long)r * a.Hq + head) * D + 2 * lane;
+        s_o0 = po[0];
+        s_o1 = po[1];
       }
-    }
+    } else {
+      float mx = -INFINITY, den = 0.f, o0 = 0.f, o1 = 0.f;
+      auto add = [&](int k, uint32_t v) {
+        const float l = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lses), k));
+        if (l == -INFINITY) return;  // uniform: no position of this split
+        float wa, wb;
+        merge_step(mx, den, l, wa, wb);
+        o0 = merge_value(o0, wa, wb, __uint_as_float(v << 16));
+        o1 = merge_value(o1, wa, wb, __uint_as_float(v & 0xFFFF0000u));
+      };
+      const bf16_t* po = (const bf16_t*)a.part_o + ((long long)r * a.Hq + head) * D + 2 * lane;
+      if (first) {
+#pragma unroll
+        for (int k = 0; k < kPrefetch; ++k)
+          if (k < S) add(k, pre[k]);
+      }
 #pragma unroll 1
-    for (int k = kPrefetch; k < S; ++k) {  // splits past the prefetched ones (long prompts)
-      const uint32_t v = *(const uint32_t*)(po + k * pstep);
-      const float wk = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), k)) * inv;
-      o0 += wk * __uint_as_float(v << 16);
-      o1 += wk * __uint_as_float(v & 0xFFFF0000u);
+      for (int k = first ? kPrefetch : 0; k < S; ++k) add(k, *(const uint32_t*)(po + k * pstep));
+      const float inv = den > 0.f ? 1.f / den : 0.f;
+      s_lse = merge_lse(mx, den);
+      s_o0 = o0 * inv;
+      s_o1 = o1 * inv;
     }
-    s_lse = den > 0.f ? mx + __logf(den) : -INFINITY;
-    s_o0 = o0;
-    s_o1 = o1;
   };
   bool combined = false;
   // the row's own positions: first its prefix positions the split kernel left
@@ -820,7 +911,7 @@ __global__ __launch_bounds__(256) void attn_tail_merge_kernel(AttnArgs a, bf16_t
 #pragma unroll
     for (int dt = 0; dt < 8; ++dt) va[dt] = *(const u32x4*)(vr + dt * vstep);  // past the end: zeroed below
     if (!combined) {  // uniform: the first tile of the wave
-      combine_splits();
+      combine_splits(g * G + min(wave, G - 1), pre_lse, true);
       combined = true;
     }
     f32x4 sc[2];
@@ -869,7 +960,7 @@ __global__ __launch_bounds__(256) void attn_tail_merge_kernel(AttnArgs a, bf16_t
 #pragma unroll
     for (int dt = 0; dt < 8; ++dt) o[dt] = mfma16x16x32(va[dt], pb, o[dt]);
   }
-  if (!combined) combine_splits();
+  if (!combined) combine_splits(g * G + min(wave, G - 1), pre_lse, true);
   // per-wave tail states -> LDS (query q = l16, dims dt*16 + grp*4 + i)
   lsum += __shfl_xor(lsum, 16, 64);
   lsum += __shfl_xor(lsum, 32, 64);
@@ -882,7 +973,7 @@ __global__ __launch_bounds__(256) void attn_tail_merge_kernel(AttnArgs a, bf16_t
   __syncthreads();
 
   // merge: wave h handles query heads h, h+4, ...; lane holds dims 2*lane, 2*lane+1
-  auto finish = [&](int h, bool first) {
+  auto finish = [&](int h) {
     const int head = g * G + h;
     // tail state of this head (exp2 domain) from the four waves
     float tm = -INFINITY;
@@ -899,53 +990,28 @@ __global__ __launch_bounds__(256) void attn_tail_merge_kernel(AttnArgs a, bf16_t
       }
     }
     const float tail_lse = tl > 0.f ? (tm + __log2f(tl)) * kLn2 : -INFINITY;
-    if (first) {  // the prefix splits are combined already: two partials left
-      const float mx = fmaxf(s_lse, tail_lse);
-      const float ws = s_lse == -INFINITY ? 0.f : __expf(s_lse - mx);
-      const float wt = tail_lse == -INFINITY ? 0.f : __expf(tail_lse - mx);
-      const float den = ws + wt;
-      const float inv = den > 0.f ? 1.f / den : 0.f;
-      const float ft = tl > 0.f ? wt * inv / tl : 0.f;  // applied to the unnormalised tail sum
-      const float fs = ws * inv;
-      *(uint32_t*)(out + ((long long)r * a.Hq + head) * D + 2 * lane) =
-          pack_bf16x2(fs * s_o0 + ft * to0, fs * s_o1 + ft * to1);
-      return;
-    }
-    // further heads (G > 4): split log-sum-exps, lane sp holds split sp's
-    const float ls = lane < S ? a.part_lse[((long long)lane * R + r) * a.Hq + head] : -INFINITY;
-    float mx = fmaxf(ls, tail_lse);
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-    const float w = ls == -INFINITY ? 0.f : __expf(ls - mx);
+    // the prefix splits are combined already: two partials left
+    const float mx = fmaxf(s_lse, tail_lse);
+    const float ws = s_lse == -INFINITY ? 0.f : __expf(s_lse - mx);
     const float wt = tail_lse == -INFINITY ? 0.f : __expf(tail_lse - mx);
-    float den = w;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) den += __shfl_xor(den, off, 64);
-    den += wt;
+    const float den = ws + wt;
     const float inv = den > 0.f ? 1.f / den : 0.f;
     const float ft = tl > 0.f ? wt * inv / tl : 0.f;  // applied to the unnormalised tail sum
-    float o0 = ft * to0, o1 = ft * to1;
-    const bf16_t* po = (const bf16_t*)a.part_o + ((long long)r * a.Hq + head) * D + 2 * lane;
-    // weight of split sp sits in lane sp; fixed split order
-#pragma unroll
-    for (int k = 0; k < kMergeMaxSplits; ++k) {
-      if (k < S) {
-        const uint32_t v = *(const uint32_t*)(po + k * pstep);
-        const float wk = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), k)) * inv;
-        o0 += wk * __uint_as_float(v << 16);
-        o1 += wk * __uint_as_float(v & 0xFFFF0000u);
-      }
-    }
-    *(uint32_t*)(out + ((long long)r * a.Hq + head) * D + 2 * lane) = pack_bf16x2(o0, o1);
+    const float fs = ws * inv;
+    *(uint32_t*)(out + ((long long)r * a.Hq + head) * D + 2 * lane) =
+        pack_bf16x2(fs * s_o0 + ft * to0, fs * s_o1 + ft * to1);
   };
-  // the first head of the wave uses the combined prefix partial
-  if (wave < G) finish(wave, true);
-  for (int h = wave + 4; h < G; h += 4) finish(h, false);
+  if (wave < G) finish(wave);
+  for (int h = wave + 4; h < G; h += 4) {  // further heads (G > 4)
+    const int head = g * G + h;
+    combine_splits(head, a.part_lse[((long long)(WALKED ? 0 : min(lane, S - 1)) * R + r) * a.Hq + head], false);
+    finish(h);
+  }
 }
 
 }  // namespace
 
-hipError_t attn_prefix_bf16(const AttnArgs& a, hipStream_t s) {
+hipError_t attn_prefix_bf16(const AttnArgs& a, bf16_t* out, hipStream_t s) {
   if (a.D != 128 || a.Hq / a.Hkv > RGD_ATTN_QV || a.split_len % 64 || a.kv.VP % 64) return hipErrorInvalidValue;
   if (a.splits <= 0 || a.nrblocks <= 0) return hipSuccess;
   if (!a.rblocks) return hipErrorInvalidValue;
@@ -954,8 +1020,12 @@ hipError_t attn_prefix_bf16(const AttnArgs& a, hipStream_t s) {
     AttnArgs b = a;
     const int n = std::min(kAttnInlineBlocks, a.nrblocks - c0);
     for (int i = 0; i < n; ++i) b.rblk[i] = a.rblocks[c0 + i];
-    hipLaunchKernelGGL((attn_prefix_kernel<RGD_ATTN_NW, RGD_ATTN_QV / 16 / RGD_ATTN_NW>), dim3(a.splits, a.Hkv, n),
-                       dim3(RGD_ATTN_NW * 64), 0, s, b);
+    if (a.walk)
+      hipLaunchKernelGGL((attn_prefix_kernel<RGD_ATTN_NW, RGD_ATTN_QV / 16 / RGD_ATTN_NW, true>),
+                         dim3(1, a.Hkv, n), dim3(RGD_ATTN_NW * 64), 0, s, b, out);
+    else
+      hipLaunchKernelGGL((attn_prefix_kernel<RGD_ATTN_NW, RGD_ATTN_QV / 16 / RGD_ATTN_NW, false>),
+                         dim3(a.splits, a.Hkv, n), dim3(RGD_ATTN_NW * 64), 0, s, b, out);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -997,7 +1067,12 @@ hipError_t attn_tail_merge_bf16(const AttnArgs& a, bf16_t* out, hipStream_t s) {
   if (a.D != 128 || a.Hq / a.Hkv > 16 || a.splits > kMergeMaxSplits || a.splits < 1 ||
       (a.tail_len > 0 && (!a.rows.pages || a.kv.page_size % 8)))
     return hipErrorInvalidValue;
-  hipLaunchKernelGGL(attn_tail_merge_kernel, dim3(a.rows.R, a.Hkv), dim3(256), 0, s, a, out);
+  if (a.walk) {  // only the rows with positions left
+    if (a.nleft > 0)
+      hipLaunchKernelGGL(attn_tail_merge_kernel<true>, dim3(a.nleft, a.Hkv), dim3(256), 0, s, a, out, a.left);
+  } else {
+    hipLaunchKernelGGL(attn_tail_merge_kernel<false>, dim3(a.rows.R, a.Hkv), dim3(256), 0, s, a, out, (const int*)nullptr);
+  }
   return hipGetLastError();
 }
 

@@ -145,13 +145,18 @@ struct AttnArgs {
   const int4* rblocks; int nrblocks;
   int4 rblk[kAttnInlineBlocks];
   int splits; int split_len;          // prefix splits (part index 0..splits-1)
+  // bf16 prefill of many rows: a workgroup walks over all splits of its row block
+  // instead of one workgroup per split;
+  // `left` (dev [nleft]) lists the rows whose last positions go to the tail kernel
+  int walk; const int* left; int nleft;
   // tail part
   int tail_len;             // visible tail positions (decode), 0 for prefill
   int tail_chunk; int tail_chunks;    // part index splits .. splits+tail_chunks-1
 };
 // bf16, head_dim 128: prefix-split partials 0 .. splits-1 on MFMA, row blocks
-// of up to RGD_ATTN_QV query vectors of one prompt
-hipError_t attn_prefix_bf16(const AttnArgs& a, hipStream_t s);
+// of up to RGD_ATTN_QV query vectors of one prompt; walks write the output of the
+// rows that have no positions left
+hipError_t attn_prefix_bf16(const AttnArgs& a, bf16_t* out, hipStream_t s);
 // bf16, head_dim 128, G <= 16: each row's paged tail on MFMA, merged with the
 // prefix-split partials into the final output
 hipError_t attn_tail_merge_bf16(const AttnArgs& a, bf16_t* out, hipStream_t s);

@@ -131,7 +131,7 @@ struct rgd_model {
   unsigned long long* soft_keys = nullptr;  // soft gate: per-chunk top-K keys [R][nchunks][kMaxTopK]
   float* soft_cm = nullptr;                 // soft gate: chunk maxima and sums [2][R][nchunks]
   // per-call row arrays
-  int* d_rows = nullptr;  // row arrays of a call without tails [3][R] (see RowArrays)
+  int* d_rows = nullptr;  // row arrays of a call without tails, [4 R] (see RowArrays)
   // pinned staging for uploads, used as a ring: an upload takes a run of ints
   // and an event that marks its copy's end
   static constexpr int kUploads = 4;
@@ -292,6 +292,11 @@ struct HostRows {
   std::vector<int> prompt, base, plen;
   std::vector<int4> blocks;  // row blocks of one prompt for the MFMA attention path
   int maxplen = 0;
+  // a prefill whose attention walks over all splits; these rows (host, device)
+  // have positions left for the tail kernel
+  bool walk = false;
+  std::vector<int> left;
+  const int* d_left = nullptr;
 };
 
 // Row blocks of one prompt for the shared-prefix attention kernel: up to
@@ -316,12 +321,32 @@ void build_blocks(const rgd_model* m, HostRows& h) {
 
 // Row arrays of a step on the device, one upload: prompt [R], base [R], plen [R],
 // then the page table [R][width] of a call with tails (width: the pages a row
-// uses, at least 1).
+// uses, at least 1) or the rows with positions left after a walk.
 struct RowArrays {
   const int* p = nullptr;
   int R = 0, width = 0;
   const int* prompt() const { return p; }
 };
+
+// Whether a prefill chunk's attention walks over the prefix splits, one workgroup
+// per (row block, KV head), instead of one workgroup per split whose partials
+// the tail kernel merges for every row.  A walk writes no partials (a 2048-row
+// chunk at 4096 positions: 210 MB) and most rows need no tail kernel, but it leaves the
+// chip idle when there are few row blocks, which only short prompts make up for.
+// Measured (8 KV heads, whole prefill of one layer, us, walk / splits): 2048-row chunks
+// of a 4096-token prompt 2385 / 2720, 1024 rows of 1024 tokens 858 / 932, 512
+// rows 567 / 581; with 64 workgroups 256-row chunks of eight 1000-token prompts
+// 8352 / 8522, of a 4096-token prompt 4353 / 4083.
+void plan_walk(const rgd_model* m, const rgd_kv* kv, HostRows& h) {
+  h.walk = false;
+  h.left.clear();
+  const long long wgs = (long long)h.blocks.size() * m->cfg.n_kv_heads;
+  if (!m->bf16 || wgs < 32 || (wgs < 128 && h.maxplen > 1024)) return;
+  h.walk = true;
+  const int len = kv->layer(0).split_len;
+  for (size_t r = 0; r < h.plen.size(); ++r)
+    if (prefix_part_end(h.plen[r], len) != h.plen[r]) h.left.push_back((int)r);
+}
 
 // pages null: a call without tails
 int upload_rows(rgd_model* m, rgd_kv* kv, const HostRows& h, const std::vector<int>* pages, RowArrays& out, hipStream_t s) {
@@ -332,6 +357,7 @@ int upload_rows(rgd_model* m, rgd_kv* kv, const HostRows& h, const std::vector<i
   all.insert(all.end(), h.base.begin(), h.base.end());
   all.insert(all.end(), h.plen.begin(), h.plen.end());
   if (pages) all.insert(all.end(), pages->begin(), pages->end());
+  else all.insert(all.end(), h.left.begin(), h.left.end());
   int* dst = pages ? kv->d_rows : m->d_rows;
   out.p = dst;
   out.R = (int)R;
@@ -383,6 +409,9 @@ int run_attention(rgd_model* m, const void* q, const KVLayout& kvl, const Rows& 
   a.part_lse = m->part_lse;
   a.rblocks = h.blocks.data();
   a.nrblocks = (int)h.blocks.size();
+  a.walk = h.walk;
+  a.left = h.d_left;
+  a.nleft = (int)h.left.size();
   a.tail_len = tail_len;
   a.tail_chunk = kTailChunk;
   a.tail_chunks = 0;  // tails are attended inside the merge kernel
@@ -412,7 +441,7 @@ int run_attention(rgd_model* m, const void* q, const KVLayout& kvl, const Rows& 
   if (m->bf16) {
     {
       TimeScope tp(m, RGD_TIMER_ATTN_PREFIX, s);
-      HIP_OK(attn_prefix_bf16(a, s));
+      HIP_OK(attn_prefix_bf16(a, (bf16_t*)out, s));
     }
     HIP_OK(attn_tail_merge_bf16(a, (bf16_t*)out, s));
   } else {
@@ -800,7 +829,7 @@ int32_t rgd_model_create(const rgd_model_config* cfg, const rgd_weights* w, int3
   A(&m->d_gate, (size_t)(2 * R + 1) * 4);
   A(&m->soft_keys, (size_t)R * m->nchunks * kMaxTopK * 8);
   A(&m->soft_cm, (size_t)2 * R * m->nchunks * 4);
-  A(&m->d_rows, (size_t)3 * R * 4);
+  A(&m->d_rows, (size_t)4 * R * 4);
   // RoPE rotations: angle pos * theta^(-2j/D) in fp64, rounded to fp32 once
   const int half = D / 2;
   const size_t ncs = ((size_t)cfg->max_pos + 1) * half;
@@ -1006,9 +1035,11 @@ int prefill_impl(rgd_model* m, rgd_kv* kv, const int32_t* tokens, int32_t B, int
           h.plen.push_back(pos + 1);
         }
       build_blocks(m, h);
+      plan_walk(m, kv, h);
       const int R = (int)h.prompt.size();
       RowArrays ra;
       RGD_TRY(upload_rows(m, kv, h, nullptr, ra, s));
+      h.d_left = ra.p + 3 * R;
       Rows rows = device_rows(ra, 0, true);
       const int* feed = tokens + (long long)b0 * n + i0;
       // the prompts' last positions: rows bb * n + n - 1 (whole prompts), or

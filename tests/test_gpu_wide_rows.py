@@ -48,11 +48,15 @@ def _prefill(rgd, t, world, dims, tokens, max_rows):
 # (d, ffn, heads, kv heads, vocab), prompts, tokens, max_rows of the wide run:
 # one partial tile past 256 rows; 2 + 1 tiles with an odd step count per split
 # (88 steps over 8 splits) and an uneven split (22 steps over 4); chunks whose
-# projections add their splits themselves (2100 rows, a 52-row last tile); rows
-# of several prompts in one chunk
+# projections add their splits themselves (2100 rows, a 52-row last tile), with
+# four and with eight heads per KV head; rows of several prompts in one chunk,
+# with prefix splits of one and of three 64-position tiles.  The wide runs of all
+# but the first walk over the prefix splits in the attention, the narrow ones
+# attend split by split.
 CASES = [((1024, 2816, 8, 4, 512), 1, 257, 300), ((1024, 5632, 8, 2, 512), 1, 700, 513),
          ((1024, 1408, 8, 2, 512), 1, 600, 600), ((1024, 3584, 8, 2, 512), 1, 2100, 2100),
-         ((4096, 1152, 32, 8, 512), 3, 230, 700)]
+         ((1024, 1408, 8, 1, 512), 1, 2100, 2100),
+         ((4096, 1152, 32, 8, 512), 3, 230, 700), ((1024, 1408, 8, 8, 512), 2, 1300, 2600)]
 
 
 @pytest.mark.parametrize("dims,prompts,n,rows", CASES)
