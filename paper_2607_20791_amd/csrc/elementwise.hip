@@ -11,6 +11,11 @@ namespace {
 
 constexpr int kNormThreads = 1024;
 
+__global__ __launch_bounds__(256) void copy_rows_kernel(const uint32_t* src, size_t stride, uint32_t* dst, int words) {
+  const uint32_t* s = (const uint32_t*)((const char*)src + blockIdx.x * stride);
+  for (int i = threadIdx.x; i < words; i += 256) dst[(size_t)blockIdx.x * words + i] = s[i];
+}
+
 template <typename T>
 __global__ __launch_bounds__(kNormThreads) void embed_rmsnorm_kernel(const int* tok, int tok_stride,
                                                                    const int* tok_map, const T* E, int d, int V,
@@ -157,6 +162,13 @@ hipError_t embed_rmsnorm(const int* tok, int tok_stride, const int* tok_map, int
   if (d % 4 || d > kChunks * 4 * kNormThreads) return hipErrorInvalidValue;
   hipLaunchKernelGGL(embed_rmsnorm_kernel<T>, dim3(R), dim3(kNormThreads), 0, s, tok, tok_stride, tok_map, E, d,
                      V, x, g, eps, xn);
+  return hipGetLastError();
+}
+
+hipError_t copy_rows(const void* src, size_t stride, void* dst, size_t bytes, int n, hipStream_t s) {
+  if (bytes % 4 || stride % 4 || n < 1) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(copy_rows_kernel, dim3(n), dim3(256), 0, s, (const uint32_t*)src, stride, (uint32_t*)dst,
+                     (int)(bytes / 4));
   return hipGetLastError();
 }
 

@@ -92,6 +92,8 @@ __host__ __device__ inline int prefix_part_end(int plen, int split_len) {
 }
 
 // ------------------------------------------------------------ elementwise ----
+// row r of n rows of `bytes` bytes (a multiple of 4): src + r * stride -> dst + r * bytes
+hipError_t copy_rows(const void* src, size_t stride, void* dst, size_t bytes, int n, hipStream_t s);
 // x[r] = E[tok[i * tok_stride]] with i = tok_map[r] (tok_map null: i = r), ids
 // clamped to [0, V); xn[r] = rmsnorm(x[r]) * g
 template <typename T>

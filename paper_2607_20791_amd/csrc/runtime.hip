@@ -118,6 +118,7 @@ struct rgd_model {
   void* act = nullptr;
   float* down_part = nullptr;
   float* logits = nullptr;
+  void* last_h = nullptr;  // prefill: final hidden rows of finished prompts [R][d]
   float* tilemax = nullptr;
   unsigned long long* tilekey = nullptr;  // [R][ntiles] LM-head argmax keys (bf16 models)
   float* chunk_sums = nullptr;
@@ -816,6 +817,7 @@ int32_t rgd_model_create(const rgd_model_config* cfg, const rgd_weights* w, int3
   A(&m->act, (size_t)R * cfg->ffn_dim * e);
   A(&m->down_part, PR * d * 4);
   A(&m->logits, (size_t)R * cfg->vocab * 4);
+  A(&m->last_h, (size_t)R * d * e);
   A(&m->tilemax, (size_t)R * m->ntiles * 4);
   A(&m->tilekey, (size_t)R * m->ntiles * 8);
   A(&m->chunk_sums, (size_t)R * m->nchunks * 4);
@@ -1022,6 +1024,18 @@ int prefill_impl(rgd_model* m, rgd_kv* kv, const int32_t* tokens, int32_t B, int
   // chunks: whole prompts when n fits in max_rows, else segments of one prompt
   const int per_chunk = n <= m->max_rows ? m->max_rows / n : 0;
   const int seg = n <= m->max_rows ? n : m->max_rows;
+  // The prompts' last hidden rows are gathered and go through the LM head
+  // together, up to max_rows of them: it streams the same weights for one row as
+  // for many (8B-class head, 160 us).  A single chunk's rows are read in place.
+  const size_t row_bytes = (size_t)d * m->esz;
+  int held = 0;  // rows in last_h, of prompts first_held ..
+  int first_held = 0;
+  auto flush_held = [&]() -> int {
+    if (held) RGD_TRY(lm_head(m, m->last_h, d, held, last_logits + (long long)first_held * V, s));
+    first_held += held;
+    held = 0;
+    return RGD_OK;
+  };
   for (int b0 = 0; b0 < B;) {
     const int nb = per_chunk ? std::min(per_chunk, B - b0) : 1;
     for (int i0 = 0; i0 < n; i0 += seg) {
@@ -1047,20 +1061,23 @@ int prefill_impl(rgd_model* m, rgd_kv* kv, const int32_t* tokens, int32_t B, int
       Readout ro{cls_layer, cls_w, cls_b, per_chunk ? n - 1 : len - 1, per_chunk ? n : 1, per_chunk ? nb : 1,
                  scores + b0};
       const Readout* rop = (cls_w && (per_chunk || i0 + len == n)) ? &ro : nullptr;
-      if (per_chunk) {
-        RGD_TRY(forward_rows(m, kv, rows, h, feed, 1, s, false, rop));
-        // logits of each prompt's last token: rows (bb * n + n - 1)
-        RGD_TRY(lm_head(m, (const char*)m->xn + (size_t)(n - 1) * d * m->esz, n * d, nb,
-                        last_logits + (long long)b0 * V, s));
-      } else {
-        RGD_TRY(forward_rows(m, kv, rows, h, feed, 1, s, false, rop));
-        if (i0 + len == n)
-          RGD_TRY(lm_head(m, (const char*)m->xn + (size_t)(len - 1) * d * m->esz, d, 1,
-                          last_logits + (long long)b0 * V, s));
+      RGD_TRY(forward_rows(m, kv, rows, h, feed, 1, s, false, rop));
+      if (!per_chunk && i0 + len < n) continue;
+      // each prompt's last token: rows bb * n + n - 1 of a chunk of whole
+      // prompts, else the segment's last row
+      const int row0 = per_chunk ? n - 1 : len - 1, stride = per_chunk ? n : 1;
+      const char* x0 = (const char*)m->xn + (size_t)row0 * row_bytes;
+      if (nb == B) {
+        RGD_TRY(lm_head(m, x0, stride * d, nb, last_logits, s));
+        continue;
       }
+      if (held + nb > m->max_rows) RGD_TRY(flush_held());
+      HIP_OK(copy_rows(x0, stride * row_bytes, (char*)m->last_h + (size_t)held * row_bytes, row_bytes, nb, s));
+      held += nb;
     }
     b0 += nb;
   }
+  RGD_TRY(flush_held());
   for (int b = 0; b < B; ++b) kv->plen[b] = start_pos + n;
   return RGD_OK;
 }

@@ -52,11 +52,13 @@ def _prefill(rgd, t, world, dims, tokens, max_rows):
 # four and with eight heads per KV head; rows of several prompts in one chunk,
 # with prefix splits of one and of three 64-position tiles.  The wide runs of all
 # but the first walk over the prefix splits in the attention, the narrow ones
-# attend split by split.
+# attend split by split.  The last two: last rows that go through the LM head
+# prompt by prompt's chunk (held back, in two lots for 70 prompts) and in place.
 CASES = [((1024, 2816, 8, 4, 512), 1, 257, 300), ((1024, 5632, 8, 2, 512), 1, 700, 513),
          ((1024, 1408, 8, 2, 512), 1, 600, 600), ((1024, 3584, 8, 2, 512), 1, 2100, 2100),
          ((1024, 1408, 8, 1, 512), 1, 2100, 2100),
-         ((4096, 1152, 32, 8, 512), 3, 230, 700), ((1024, 1408, 8, 8, 512), 2, 1300, 2600)]
+         ((4096, 1152, 32, 8, 512), 3, 230, 700), ((1024, 1408, 8, 8, 512), 2, 1300, 2600),
+         ((1024, 128, 8, 2, 512), 5, 30, 150), ((1024, 128, 8, 2, 512), 70, 1, 70)]
 
 
 @pytest.mark.parametrize("dims,prompts,n,rows", CASES)
