@@ -742,21 +742,31 @@ __global__ __launch_bounds__(256) void attn_tail_combine_kernel(AttnArgs a, floa
   }
 }
 
-// Tail attention fused with the merge, bf16 caches: one workgroup of four
-// waves per (row, KV head).  Each wave attends 32-position tiles of the row's
-// paged tail (tiles wave, wave+4, ...) with MFMA: the G query heads of the KV
-// head form one 16-column tile, K and V^T fragments are loaded straight from
-// the pages (K rows in the gathered order of the prefix kernel, so every lane
-// ends up with eight consecutive positions).  The four waves' tail states are
-// merged through LDS, and wave h writes query head h's output.  The merge is
-// in log-sum-exp form: a head's prefix-split partials are combined in split order
-// (for the wave's first head while its first tile is loading), which leaves a
-// two-term merge with the tail after the exchange.  WALKED: the splits come
-// combined, as one fp32 partial, and the rows are those of a list.
+// Tail attention fused with the merge, bf16 caches: one workgroup per (row, KV
+// head).  The row's 32-position tiles (the last positions of its prefix, then its
+// paged tail) are dealt to four lanes of work in turn (tile t to lane t % 4), each
+// attended with MFMA into a state of its own: the G query heads of the KV head
+// form one 16-column tile, K and V^T fragments are loaded straight from the pages
+// (K rows in the gathered order of the prefix kernel, so every lane ends up with
+// eight consecutive positions).  The four states are merged through LDS in a fixed
+// order, and a head's output is written by one wave.  The merge is in log-sum-exp
+// form: a head's prefix-split partials are combined in split order (for the wave's
+// first head while its first tile is loading), which leaves a two-term merge with
+// the tail after the exchange.
+// NWV: waves per workgroup.  Four take one lane of work each: the shortest chain,
+// for few (row, head) pairs.  One takes all four in turn: a workgroup's start and
+// merge cost more than a tile, and with enough pairs to fill the chip fewer, longer
+// waves pay them once instead of four times.  Attention stage of 256 rows x 8 KV heads
+// over 1024-position prompts, four waves / one: tails of 4 positions 56.9 / 47.9 us,
+// 64 59.8 / 55.6, 200 84.4 / 81.9.  The states and their merge are the same, so the
+// bits are too.
+// GM: query heads per KV head at most (LDS).
+// WALKED: the splits come combined, as one fp32 partial, and the rows are those of
+// a list.
 constexpr int kMergeMaxSplits = 64;
 
-template <bool WALKED>
-__global__ __launch_bounds__(256) void attn_tail_merge_kernel(AttnArgs a, bf16_t* out, const int* rowlist) {
+template <bool WALKED, int NWV, int GM>
+__global__ __launch_bounds__(NWV * 64) void attn_tail_merge_kernel(AttnArgs a, bf16_t* out, const int* rowlist) {
   constexpr int D = 128, TT = 32;
   const int r = WALKED ? rowlist[blockIdx.x] : blockIdx.x, g = blockIdx.y;
   const int G = a.Hq / a.Hkv;
@@ -766,8 +776,8 @@ __global__ __launch_bounds__(256) void attn_tail_merge_kernel(AttnArgs a, bf16_t
   const int ps = a.kv.page_size;
   const float scale = rsqrtf(float(D)) * kLog2e;
 
-  __shared__ float w_m[4][16], w_l[4][16];
-  __shared__ __attribute__((aligned(16))) float w_o[4][16][D + 4];  // [wave][query][dim]
+  __shared__ float w_m[4][GM], w_l[4][GM];
+  __shared__ __attribute__((aligned(16))) float w_o[4][GM][D + 4];  // [lane of work][query][dim]
 
   // First requests: the row's visible prefix length and its first 64 tail
   // page numbers (lane i holds page i), so that tile addresses need no
@@ -821,10 +831,6 @@ __global__ __launch_bounds__(256) void attn_tail_merge_kernel(AttnArgs a, bf16_t
       qf[ks] = ok ? x : u32x4{0u, 0u, 0u, 0u};
     }
   }
-  float m = -INFINITY, lsum = 0.f;
-  f32x4 o[8];
-#pragma unroll
-  for (int dt = 0; dt < 8; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
   // The prefix splits of one head combined into one partial (log-sum-exp
   // s_lse, normalised output s_o0 / s_o1 for dims 2*lane, 2*lane+1).  It needs no
   // tail data: the first head's is formed while the first tile's loads are in
@@ -874,105 +880,115 @@ __global__ __launch_bounds__(256) void attn_tail_merge_kernel(AttnArgs a, bf16_t
   const long long bg = (long long)prompt * a.Hkv + g;
   const bf16_t* pk = (const bf16_t*)a.kv.prefix_k + bg * a.kv.P * D;
   const bf16_t* pv = (const bf16_t*)a.kv.prefix_v + bg * a.kv.VP * D;
-  for (int vt = wave; vt < n_all; vt += 4) {
-    const bool ov = vt < n_ovt;
-    const int tb = ov ? pe + vt * TT : (vt - n_ovt) * TT;  // first position of the tile
-    const int lim = ov ? plen : n;                          // positions < lim exist
-    // every address of the tile first (page numbers come from registers),
-    // then all its loads back to back
-    int kp[2];
+#pragma unroll 1
+  for (int w = wave; w < 4; w += NWV) {
+    float m = -INFINITY, lsum = 0.f;
+    f32x4 o[8];
 #pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      const int pos = tb + k_gather_row(0, e, l16);
-      kp[e] = pos < lim ? pos : tb;
-    }
-    // this lane's eight positions p0 .. p0+7 lie in one page (ps % 8 == 0) or
-    // one 64-position block of the prefix V layout (p0 % 8 == 0)
-    const int p0 = tb + grp * 8;
-    const int nv = lim - p0;
-    const int vp = nv > 0 ? p0 : tb;
-    const int kpg0 = page_at(ov ? 0 : kp[0] / ps), kpg1 = page_at(ov ? 0 : kp[1] / ps);
-    const int vpg = page_at(ov ? 0 : vp / ps);
-    const bf16_t* kr[2];
+    for (int dt = 0; dt < 8; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int vt = w; vt < n_all; vt += 4) {
+      const bool ov = vt < n_ovt;
+      const int tb = ov ? pe + vt * TT : (vt - n_ovt) * TT;  // first position of the tile
+      const int lim = ov ? plen : n;                          // positions < lim exist
+      // every address of the tile first (page numbers come from registers),
+      // then all its loads back to back
+      int kp[2];
 #pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      const int pg = e ? kpg1 : kpg0;
-      kr[e] = ov ? pk + (long long)kp[e] * D + grp * 8
-                 : (const bf16_t*)a.kv.pool_k + (((long long)pg * a.Hkv + g) * ps + kp[e] % ps) * D + grp * 8;
-    }
-    const bf16_t* vr = ov ? pv + ((long long)(vp / 64) * D + l16) * 64 + vp % 64
-                          : (const bf16_t*)a.kv.pool_v + (((long long)vpg * a.Hkv + g) * D + l16) * ps + vp % ps;
-    const long long vstep = ov ? 16LL * 64 : 16LL * ps;  // 16 head-dim rows
-    u32x4 ka[2][4], va[8];
-#pragma unroll
-    for (int e = 0; e < 2; ++e)
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks) ka[e][ks] = *(const u32x4*)(kr[e] + ks * 32);  // past the end: masked scores
-#pragma unroll
-    for (int dt = 0; dt < 8; ++dt) va[dt] = *(const u32x4*)(vr + dt * vstep);  // past the end: zeroed below
-    if (!combined) {  // uniform: the first tile of the wave
-      combine_splits(g * G + min(wave, G - 1), pre_lse, true);
-      combined = true;
-    }
-    f32x4 sc[2];
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      sc[e] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks) sc[e] = mfma16x16x32(ka[e][ks], qf[ks], sc[e]);
-    }
-    float x = -INFINITY;
-#pragma unroll
-    for (int e = 0; e < 2; ++e)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        if (p0 + e * 4 + i >= lim) sc[e][i] = -INFINITY;
-        x = fmaxf(x, sc[e][i]);
+      for (int e = 0; e < 2; ++e) {
+        const int pos = tb + k_gather_row(0, e, l16);
+        kp[e] = pos < lim ? pos : tb;
       }
-    x = fmaxf(x, __shfl_xor(x, 16, 64));
-    x = fmaxf(x, __shfl_xor(x, 32, 64));
-    x *= scale;
-    if (x > m) {
-      const float alpha = exp2_raw(m - x);
-      lsum *= alpha;
+      // this lane's eight positions p0 .. p0+7 lie in one page (ps % 8 == 0) or
+      // one 64-position block of the prefix V layout (p0 % 8 == 0)
+      const int p0 = tb + grp * 8;
+      const int nv = lim - p0;
+      const int vp = nv > 0 ? p0 : tb;
+      const int kpg0 = page_at(ov ? 0 : kp[0] / ps), kpg1 = page_at(ov ? 0 : kp[1] / ps);
+      const int vpg = page_at(ov ? 0 : vp / ps);
+      const bf16_t* kr[2];
 #pragma unroll
-      for (int dt = 0; dt < 8; ++dt) o[dt] *= alpha;
-      m = x;
-    }
-    const float msub = m == -INFINITY ? INFINITY : m;
-    float p[8];
+      for (int e = 0; e < 2; ++e) {
+        const int pg = e ? kpg1 : kpg0;
+        kr[e] = ov ? pk + (long long)kp[e] * D + grp * 8
+                   : (const bf16_t*)a.kv.pool_k + (((long long)pg * a.Hkv + g) * ps + kp[e] % ps) * D + grp * 8;
+      }
+      const bf16_t* vr = ov ? pv + ((long long)(vp / 64) * D + l16) * 64 + vp % 64
+                            : (const bf16_t*)a.kv.pool_v + (((long long)vpg * a.Hkv + g) * D + l16) * ps + vp % ps;
+      const long long vstep = ov ? 16LL * 64 : 16LL * ps;  // 16 head-dim rows
+      u32x4 ka[2][4], va[8];
 #pragma unroll
-    for (int e = 0; e < 2; ++e)
+      for (int e = 0; e < 2; ++e)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) p[e * 4 + i] = exp2_raw(fmaf(sc[e][i], scale, -msub));
+        for (int ks = 0; ks < 4; ++ks) ka[e][ks] = *(const u32x4*)(kr[e] + ks * 32);  // past the end: masked scores
 #pragma unroll
-    for (int i = 0; i < 8; ++i) lsum += p[i];
-    const u32x4 pb = {pack2(p[0], p[1]), pack2(p[2], p[3]), pack2(p[4], p[5]), pack2(p[6], p[7])};
-    if (nv < 8) {  // V past the row's end is arbitrary (unwritten slots): zero it
+      for (int dt = 0; dt < 8; ++dt) va[dt] = *(const u32x4*)(vr + dt * vstep);  // past the end: zeroed below
+      if (!combined) {  // uniform: the first tile of the wave
+        combine_splits(g * G + min(wave, G - 1), pre_lse, true);
+        combined = true;
+      }
+      f32x4 sc[2];
 #pragma unroll
-      for (int dt = 0; dt < 8; ++dt)
+      for (int e = 0; e < 2; ++e) {
+        sc[e] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {
-          if (2 * w >= nv) va[dt][w] = 0u;
-          else if (2 * w + 1 >= nv) va[dt][w] &= 0xFFFFu;
+        for (int ks = 0; ks < 4; ++ks) sc[e] = mfma16x16x32(ka[e][ks], qf[ks], sc[e]);
+      }
+      float x = -INFINITY;
+#pragma unroll
+      for (int e = 0; e < 2; ++e)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          if (p0 + e * 4 + i >= lim) sc[e][i] = -INFINITY;
+          x = fmaxf(x, sc[e][i]);
         }
-    }
+      x = fmaxf(x, __shfl_xor(x, 16, 64));
+      x = fmaxf(x, __shfl_xor(x, 32, 64));
+      x *= scale;
+      if (x > m) {
+        const float alpha = exp2_raw(m - x);
+        lsum *= alpha;
 #pragma unroll
-    for (int dt = 0; dt < 8; ++dt) o[dt] = mfma16x16x32(va[dt], pb, o[dt]);
+        for (int dt = 0; dt < 8; ++dt) o[dt] *= alpha;
+        m = x;
+      }
+      const float msub = m == -INFINITY ? INFINITY : m;
+      float p[8];
+#pragma unroll
+      for (int e = 0; e < 2; ++e)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) p[e * 4 + i] = exp2_raw(fmaf(sc[e][i], scale, -msub));
+#pragma unroll
+      for (int i = 0; i < 8; ++i) lsum += p[i];
+      const u32x4 pb = {pack2(p[0], p[1]), pack2(p[2], p[3]), pack2(p[4], p[5]), pack2(p[6], p[7])};
+      if (nv < 8) {  // V past the row's end is arbitrary (unwritten slots): zero it
+#pragma unroll
+        for (int dt = 0; dt < 8; ++dt)
+#pragma unroll
+          for (int w = 0; w < 4; ++w) {
+            if (2 * w >= nv) va[dt][w] = 0u;
+            else if (2 * w + 1 >= nv) va[dt][w] &= 0xFFFFu;
+          }
+      }
+#pragma unroll
+      for (int dt = 0; dt < 8; ++dt) o[dt] = mfma16x16x32(va[dt], pb, o[dt]);
+    }
+    // tail state -> LDS (query q = l16, dims dt*16 + grp*4 + i)
+    lsum += __shfl_xor(lsum, 16, 64);
+    lsum += __shfl_xor(lsum, 32, 64);
+    if (l16 < GM) {
+      if (grp == 0) {
+        w_m[w][l16] = m;
+        w_l[w][l16] = lsum;
+      }
+#pragma unroll
+      for (int dt = 0; dt < 8; ++dt) *(f32x4*)&w_o[w][l16][dt * 16 + grp * 4] = o[dt];
+    }
   }
   if (!combined) combine_splits(g * G + min(wave, G - 1), pre_lse, true);
-  // per-wave tail states -> LDS (query q = l16, dims dt*16 + grp*4 + i)
-  lsum += __shfl_xor(lsum, 16, 64);
-  lsum += __shfl_xor(lsum, 32, 64);
-  if (grp == 0) {
-    w_m[wave][l16] = m;
-    w_l[wave][l16] = lsum;
-  }
-#pragma unroll
-  for (int dt = 0; dt < 8; ++dt) *(f32x4*)&w_o[wave][l16][dt * 16 + grp * 4] = o[dt];
   __syncthreads();
 
-  // merge: wave h handles query heads h, h+4, ...; lane holds dims 2*lane, 2*lane+1
+  // merge: wave h handles query heads h, h + NWV, ...; lane holds dims 2*lane, 2*lane+1
   auto finish = [&](int h) {
     const int head = g * G + h;
     // tail state of this head (exp2 domain) from the four waves
@@ -1002,7 +1018,7 @@ __global__ __launch_bounds__(256) void attn_tail_merge_kernel(AttnArgs a, bf16_t
         pack_bf16x2(fs * s_o0 + ft * to0, fs * s_o1 + ft * to1);
   };
   if (wave < G) finish(wave);
-  for (int h = wave + 4; h < G; h += 4) {  // further heads (G > 4)
+  for (int h = wave + NWV; h < G; h += NWV) {  // further heads
     const int head = g * G + h;
     combine_splits(head, a.part_lse[((long long)(WALKED ? 0 : min(lane, S - 1)) * R + r) * a.Hq + head], false);
     finish(h);
@@ -1067,11 +1083,20 @@ hipError_t attn_tail_merge_bf16(const AttnArgs& a, bf16_t* out, hipStream_t s) {
   if (a.D != 128 || a.Hq / a.Hkv > 16 || a.splits > kMergeMaxSplits || a.splits < 1 ||
       (a.tail_len > 0 && (!a.rows.pages || a.kv.page_size % 8)))
     return hipErrorInvalidValue;
-  if (a.walk) {  // only the rows with positions left
-    if (a.nleft > 0)
-      hipLaunchKernelGGL(attn_tail_merge_kernel<true>, dim3(a.nleft, a.Hkv), dim3(256), 0, s, a, out, a.left);
+  const int rows = a.walk ? a.nleft : a.rows.R;  // after a walk only those with positions left
+  if (rows < 1) return hipSuccess;
+  // one wave per workgroup: enough pairs for eight waves on every CU, one partial
+  // to merge per head (with 16 splits of an 8193-position prompt the serial loads of
+  // four heads' partials cost more: 117 against 111 us)
+  const int G = a.Hq / a.Hkv;
+  const bool one = G <= 4 && (a.walk || a.splits == 1) && (long long)rows * a.Hkv >= 2048;
+  const dim3 grid(rows, a.Hkv);
+  if (a.walk) {
+    if (one) hipLaunchKernelGGL((attn_tail_merge_kernel<true, 1, 4>), grid, dim3(64), 0, s, a, out, a.left);
+    else hipLaunchKernelGGL((attn_tail_merge_kernel<true, 4, 16>), grid, dim3(256), 0, s, a, out, a.left);
   } else {
-    hipLaunchKernelGGL(attn_tail_merge_kernel<false>, dim3(a.rows.R, a.Hkv), dim3(256), 0, s, a, out, (const int*)nullptr);
+    if (one) hipLaunchKernelGGL((attn_tail_merge_kernel<false, 1, 4>), grid, dim3(64), 0, s, a, out, nullptr);
+    else hipLaunchKernelGGL((attn_tail_merge_kernel<false, 4, 16>), grid, dim3(256), 0, s, a, out, nullptr);
   }
   return hipGetLastError();
 }

@@ -88,3 +88,35 @@ def test_lm_head_rows_alone_and_together(rgd, R, V):
         rgd.kernel_lm_head(m, h[r:r + 50].contiguous(), rows[r:r + 50])
     t.cuda.synchronize()
     assert t.equal(out[:R], rows) and bool((out[R] == -7.0).all())
+
+
+@pytest.mark.parametrize("heads,kv_heads", [(32, 8), (6, 2)])
+def test_tail_attention_of_many_rows(rgd, heads, kv_heads):
+    """Rows of a batch large enough for one-wave tail workgroups against the same rows few at a time (four waves):
+    prefixes that end past a split, tails of no, one and several 32-position tiles."""
+    t = torch()
+    bf = t.bfloat16
+    g = t.Generator(device="cuda").manual_seed(heads)
+    B, n, P = 2048 // kv_heads // 8, 8, 200
+    one = t.ones(128, device="cuda")
+    w = lambda *s: (t.randn(*s, generator=g, device="cuda") * 0.02).to(bf)  # noqa: E731
+    L = {"wq": w(heads * 128, 128), "wk": w(kv_heads * 128, 128), "wv": w(kv_heads * 128, 128), "wo": w(128, heads * 128),
+         "w_gate": w(128, 128), "w_up": w(128, 128), "w_down": w(128, 128), "attn_norm": one, "ffn_norm": one}
+    m = rgd.Model(rgd.ModelConfig(1, 128, heads, kv_heads, 128, 128, 128, rgd.DTYPE_BF16, 1e-5, 500000.0, 512),
+                  {"embed": w(128, 128), "final_norm": one, "lm_head": w(128, 128)}, [L], B * n)
+    R, pages = B * n, 7
+    q, k = w(R, heads, 128) * 50, w(B, kv_heads, P, 128) * 50
+    v = w(B, kv_heads, (P + 63) // 64, 128, 64)
+    tk, tv = w(R * pages, kv_heads, 16, 128) * 50, w(R * pages, kv_heads, 128, 16)
+    table = t.randperm(R * pages, generator=g, device="cuda").to(t.int32).view(R, pages)
+    prompt = [r // n for r in range(R)]
+    plen = [P - 3 * (r % 5) for r in range(R)]
+    for tail in (0, 5, 32, 101):
+        out, few = t.empty(R, heads * 128, dtype=bf, device="cuda"), t.empty(R, heads * 128, dtype=bf, device="cuda")
+        rgd.kernel_attention(m, q, prompt, plen, k, v, B, P, tk, tv, 16, table, pages, tail, out)
+        for r in range(0, R, 40):
+            e = min(R, r + 40)
+            rgd.kernel_attention(m, q[r:e].contiguous(), prompt[r:e], plen[r:e], k, v, B, P, tk, tv, 16,
+                                 table[r:e].contiguous(), pages, tail, few[r:e])
+        t.cuda.synchronize()
+        assert t.isfinite(out.float()).all() and t.equal(out, few), tail
