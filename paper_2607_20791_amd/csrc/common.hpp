@@ -58,6 +58,44 @@ RGD_DEV float wave_sum(float v) {
   return v;
 }
 
+// Block-wide reductions whose `scratch` (blockDim.x/64 values) no other code of
+// the kernel touches before: one barrier instead of two.  Same order of the sums as
+// block_sum.
+RGD_DEV float block_max_once(float v, float* scratch) {
+  v = wave_max(v);
+  const int w = threadIdx.x / kWave, nw = blockDim.x / kWave;
+  if ((threadIdx.x & 63) == 0) scratch[w] = v;
+  __syncthreads();
+  float t = -INFINITY;
+  for (int i = 0; i < nw; ++i) t = fmaxf(t, scratch[i]);
+  return t;
+}
+RGD_DEV float block_sum_once(float v, float* scratch) {
+  v = wave_sum(v);
+  const int w = threadIdx.x / kWave, nw = blockDim.x / kWave;
+  if ((threadIdx.x & 63) == 0) scratch[w] = v;
+  __syncthreads();
+  float t = 0.f;
+  for (int i = 0; i < nw; ++i) t += scratch[i];
+  return t;
+}
+// two sums at once
+RGD_DEV void block_sums_once(float& a, float& b, float* sa, float* sb) {
+  a = wave_sum(a);
+  b = wave_sum(b);
+  const int w = threadIdx.x / kWave, nw = blockDim.x / kWave;
+  if ((threadIdx.x & 63) == 0) {
+    sa[w] = a;
+    sb[w] = b;
+  }
+  __syncthreads();
+  a = b = 0.f;
+  for (int i = 0; i < nw; ++i) {
+    a += sa[i];
+    b += sb[i];
+  }
+}
+
 // Block-wide reductions for blockDim.x a multiple of 64 (<= 1024).  `scratch`
 // must hold blockDim.x/64 floats; the result is broadcast to every thread.
 RGD_DEV float block_sum(float v, float* scratch) {
