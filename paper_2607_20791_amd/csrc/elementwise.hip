@@ -70,88 +70,106 @@ __global__ __launch_bounds__(kNormThreads) void residual_rmsnorm_kernel(float* x
   norm_store(v, gg, d, eps, xn + (long long)r * d);
 }
 
-// One workgroup per (row, group of 8 heads of the fused q|k|v output).  The
-// rotation of position pos, pair j is (cos, sin) = rope_cs[pos][j] (a table
-// computed once on the host in fp64).
+// One workgroup per (row, kRopeThreads groups of W neighbouring rotation pairs
+// (j, j + D/2) of the fused q|k|v output), one group per thread.  The rotation
+// of position pos, pair j is (cos, sin) = rope_cs[pos][j] (a table computed once
+// on the host in fp64).
 // NP >= nparts: the loads of all NP split partials (clamped to the last one,
 // masked by a 0/1 factor) and of the rotation are issued before any of them is
 // used, so the kernel waits for memory once (a partial or a table load used
 // only under a condition is moved into a branch by the compiler, which then
 // waits for it where the branches join, one memory round trip each).
-template <typename T, int NP>
-__global__ __launch_bounds__(1024) void qkv_rope_kernel(const float* parts, int nparts, long long part_stride,
-                                                       Rows rows, int Hq, int Hkv, int D, const float2* rope_cs,
-                                                       int max_pos, T* q, KVLayout kv) {
+constexpr int kRopeThreads = 256;
+// W = 4 from this many rows (Hq + 2 Hkv = 48 heads of 128, bf16; W 1 / W 4):
+// 2048 rows 45.3 / 27.6 us, 256 rows 10.0 / 8.5; 64 rows 5.0 / 5.1, where the
+// memory round trip is all there is and the short workgroups spread wider.
+constexpr int kRopeWideRows = 128;
+
+template <typename T, int NP, int W>
+__global__ __launch_bounds__(kRopeThreads) void qkv_rope_kernel(const float* parts, int nparts, long long part_stride,
+                                                                Rows rows, int Hq, int Hkv, int D,
+                                                                const float2* rope_cs, int max_pos, T* q,
+                                                                KVLayout kv) {
+  typedef float vec __attribute__((ext_vector_type(W)));
+  typedef float vec2 __attribute__((ext_vector_type(2 * W)));
   const int r = blockIdx.x;
-  const int h0 = blockIdx.y * 8, h1 = min(h0 + 8, Hq + 2 * Hkv);
-  const int half = D / 2;
+  const int half = D / 2, groups = half / W;  // threads per head
+  const int item = blockIdx.y * kRopeThreads + threadIdx.x;
+  const int h = item / groups, j = item % groups * W;
+  if (h >= Hq + 2 * Hkv) return;
   const int pos = min(rows.prefill ? rows.base_pos[r] : rows.base_pos[r] + rows.t, max_pos);
-  const float2* cs = rope_cs + (long long)pos * half;
   const int nqkv = (Hq + 2 * Hkv) * D;
-  const float* pr = parts + (long long)r * nqkv;
-  // columns c and c + D/2, summed over the splits in split order (split-K
-  // partials are finite, so the 0/1 factor masks them exactly)
-  auto cols = [&](int c, float& v1, float& v2) {
-    float a1[NP], a2[NP];
+  const float* pr = parts + (long long)r * nqkv + h * D + j;
+  // columns j .. j + W - 1 and the same + D/2, summed over the splits in split
+  // order (split-K partials are finite, so the 0/1 factor masks them exactly)
+  vec a1[NP], a2[NP];
 #pragma unroll
-    for (int p = 0; p < NP; ++p) {
-      const float* pp = pr + min(p, nparts - 1) * part_stride;
-      a1[p] = pp[c];
-      a2[p] = pp[c + half];
-    }
-    v1 = a1[0];
-    v2 = a2[0];
-#pragma unroll
-    for (int p = 1; p < NP; ++p) {
-      const float f = p < nparts ? 1.f : 0.f;
-      v1 += a1[p] * f;
-      v2 += a2[p] * f;
-    }
-  };
+  for (int p = 0; p < NP; ++p) {
+    const float* pp = pr + min(p, nparts - 1) * part_stride;
+    a1[p] = *(const vec*)pp;
+    a2[p] = *(const vec*)(pp + half);
+  }
+  const vec2 cs = *(const vec2*)(rope_cs + (long long)pos * half + j);
   const int b = rows.prompt[r];
-  // destinations: K of head h at kd + h * kstride; V of head h, dim d at
-  // vd + h * vhstride + d * vdstride
-  T* kd;
-  T* vd;
-  long long kstride, vhstride, vdstride;
-  if (rows.prefill) {
-    kd = (T*)kv.prefix_k + ((long long)b * Hkv * kv.P + pos) * D;
-    kstride = (long long)kv.P * D;
-    vd = (T*)kv.prefix_v + ((long long)b * Hkv * (kv.VP / 64) + pos / 64) * D * 64 + pos % 64;
-    vhstride = (long long)kv.VP * D;
-    vdstride = 64;
-  } else {
-    const int ps = kv.page_size;
-    const int page = rows.pages[(long long)r * rows.max_pages + rows.t / ps];
-    const int slot = rows.t % ps;
-    kd = (T*)kv.pool_k + ((long long)page * Hkv * ps + slot) * D;
-    kstride = (long long)ps * D;
-    vd = (T*)kv.pool_v + (long long)page * Hkv * D * ps + slot;
-    vhstride = (long long)D * ps;
-    vdstride = ps;
+  vec x1 = a1[0], x2 = a2[0];
+#pragma unroll
+  for (int p = 1; p < NP; ++p) {
+    const float f = p < nparts ? 1.f : 0.f;
+    x1 += a1[p] * f;
+    x2 += a2[p] * f;
   }
-  const int nh = h1 - h0;
-  for (int i = threadIdx.x; i < nh * half; i += blockDim.x) {
-    const int h = h0 + i / half, j = i % half;
-    const int base = h * D;
-    float x1, x2;
-    cols(base + j, x1, x2);
-    // q and k pairs (j, j + D/2) are rotated, v passes through (cos 1, sin 0)
-    const float2 cj = cs[j];
-    const float kq = h < Hq + Hkv ? 1.f : 0.f;
-    const float c = cj.x * kq + (1.f - kq), sn = cj.y * kq;
-    const float y1 = x1 * c - x2 * sn;
-    const float y2 = x2 * c + x1 * sn;
-    if (h < Hq + Hkv) {
-      T* dst = h < Hq ? q + ((long long)r * Hq + h) * D : kd + (long long)(h - Hq) * kstride;
-      store_f(dst + j, y1);
-      store_f(dst + j + half, y2);
-    } else {             // v: dims j and j + D/2 of head h - Hq - Hkv
-      const int hv = h - Hq - Hkv;
-      store_f(vd + hv * vhstride + (long long)j * vdstride, y1);
-      store_f(vd + hv * vhstride + (long long)(j + half) * vdstride, y2);
+  // q and k pairs (j, j + D/2) are rotated, v passes through (cos 1, sin 0)
+  const float kq = h < Hq + Hkv ? 1.f : 0.f;
+  float y1[W], y2[W];
+#pragma unroll
+  for (int i = 0; i < W; ++i) {
+    const float c = cs[2 * i] * kq + (1.f - kq), sn = cs[2 * i + 1] * kq;
+    // one rounding order for every W: a row's bits do not depend on the launch
+    y1[i] = fmaf(x1[i], c, -(x2[i] * sn));
+    y2[i] = fmaf(x2[i], c, x1[i] * sn);
+  }
+  // destinations: the dims of a K head lie side by side, those of a V head
+  // vstride apart
+  const int ps = kv.page_size;
+  const int page = rows.prefill ? 0 : rows.pages[(long long)r * rows.max_pages + rows.t / ps];
+  const int slot = rows.prefill ? 0 : rows.t % ps;
+  if (h < Hq + Hkv) {
+    T* dst;
+    if (h < Hq) dst = q + ((long long)r * Hq + h) * D;
+    else if (rows.prefill) dst = (T*)kv.prefix_k + (((long long)b * Hkv + h - Hq) * kv.P + pos) * D;
+    else dst = (T*)kv.pool_k + (((long long)page * Hkv + h - Hq) * ps + slot) * D;
+    if constexpr (W == 4) {
+      store4(dst + j, float4{y1[0], y1[1], y1[2], y1[3]});
+      store4(dst + j + half, float4{y2[0], y2[1], y2[2], y2[3]});
+    } else {
+      store_f(dst + j, y1[0]);
+      store_f(dst + j + half, y2[0]);
+    }
+  } else {
+    const int hv = h - Hq - Hkv;
+    const long long vstride = rows.prefill ? 64 : ps;
+    T* vd = rows.prefill ? (T*)kv.prefix_v + (((long long)b * Hkv + hv) * (kv.VP / 64) + pos / 64) * D * 64 + pos % 64
+                         : (T*)kv.pool_v + ((long long)page * Hkv + hv) * D * ps + slot;
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+      store_f(vd + (j + i) * vstride, y1[i]);
+      store_f(vd + (j + half + i) * vstride, y2[i]);
     }
   }
+}
+
+template <typename T, int W>
+void launch_rope(const float* parts, int nparts, long long part_stride, const Rows& rows, int Hq, int Hkv, int D,
+                 const float* rope_cs, int max_pos, T* q, const KVLayout& kv, hipStream_t s) {
+  const dim3 grid(rows.R, ((Hq + 2 * Hkv) * (D / 2 / W) + kRopeThreads - 1) / kRopeThreads);
+  auto run = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(kRopeThreads), 0, s, parts, nparts, part_stride, rows, Hq, Hkv, D,
+                       (const float2*)rope_cs, max_pos, q, kv);
+  };
+  if (nparts == 1) run(qkv_rope_kernel<T, 1, W>);
+  else if (nparts <= 4) run(qkv_rope_kernel<T, 4, W>);
+  else if (nparts <= 8) run(qkv_rope_kernel<T, 8, W>);
+  else run(qkv_rope_kernel<T, kMaxSplitK, W>);
 }
 
 }  // namespace
@@ -193,18 +211,11 @@ hipError_t qkv_rope_store(const float* parts, int nparts, long long part_stride,
                           int Hkv, int D, const float* rope_cs, int max_pos, T* q, const KVLayout& kv,
                           hipStream_t s) {
   if (D > 256 || (D & 1) || nparts < 1 || nparts > kMaxSplitK) return hipErrorInvalidValue;
-  // one thread per (head of the group of 8, rotation pair)
-  const int threads = std::max(64, 8 * (D / 2));
-  const dim3 grid(rows.R, (Hq + 2 * Hkv + 7) / 8);
-  if (nparts <= 4)
-    hipLaunchKernelGGL((qkv_rope_kernel<T, 4>), grid, dim3(threads), 0, s, parts, nparts, part_stride, rows, Hq, Hkv,
-                       D, (const float2*)rope_cs, max_pos, q, kv);
-  else if (nparts <= 8)
-    hipLaunchKernelGGL((qkv_rope_kernel<T, 8>), grid, dim3(threads), 0, s, parts, nparts, part_stride, rows, Hq, Hkv,
-                       D, (const float2*)rope_cs, max_pos, q, kv);
+  const uintptr_t at = (uintptr_t)parts | (uintptr_t)q | (uintptr_t)kv.prefix_k | (uintptr_t)kv.pool_k;
+  if (rows.R >= kRopeWideRows && D % 8 == 0 && part_stride % 4 == 0 && at % 16 == 0)
+    launch_rope<T, 4>(parts, nparts, part_stride, rows, Hq, Hkv, D, rope_cs, max_pos, q, kv, s);
   else
-    hipLaunchKernelGGL((qkv_rope_kernel<T, kMaxSplitK>), grid, dim3(threads), 0, s, parts, nparts, part_stride, rows,
-                       Hq, Hkv, D, (const float2*)rope_cs, max_pos, q, kv);
+    launch_rope<T, 1>(parts, nparts, part_stride, rows, Hq, Hkv, D, rope_cs, max_pos, q, kv, s);
   return hipGetLastError();
 }
 
