@@ -165,3 +165,15 @@ def test_minp_ragged_last_chunk(rgd, R, V):
         for r in range(R):
             for d in range(2):
                 judge_draw(z[r], T, pmin, float(philox.uniform(int(seeds[r]), 1, d)), int(got[r, d]))
+
+
+@pytest.mark.parametrize("V", [262144, 266240, 600004])
+def test_draw_over_more_chunks_than_a_wave_has_lanes(rgd, V):
+    """64, 65 and 147 chunks of 4096 logits: the chunk search takes more than one step of 64 lanes."""
+    g = np.random.default_rng(V)
+    z = g.normal(size=(8, V)).astype(np.float32)
+    z[0, V - 1] = z[0].max() + 9    # the last chunk holds nearly all the weight
+    seeds = np.arange(8, dtype=np.uint64)
+    got = sample_gpu(rgd, z, 1.0, 0.01, seeds, ctr=0, stream0=0, draws=1)[:, 0]
+    assert got[0] == V - 1
+    _check_rows(f"min-p draw, V={V}", z, 1.0, 0.01, got, seeds, 0, 0)

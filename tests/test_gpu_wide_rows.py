@@ -120,3 +120,55 @@ def test_tail_attention_of_many_rows(rgd, heads, kv_heads):
                                  table[r:e].contiguous(), pages, tail, few[r:e])
         t.cuda.synchronize()
         assert t.isfinite(out.float()).all() and t.equal(out, few), tail
+
+
+def test_attention_reads_q_in_place_or_from_a_copy(rgd):
+    """q at a 2-byte offset, and q that is the output buffer, take the copy; both give the bits of q read in place."""
+    t = torch()
+    bf = t.bfloat16
+    g = t.Generator(device="cuda").manual_seed(3)
+    top, layers = _world(t, 3, 1024, 128, 8, 2, 128)
+    m = rgd.Model(rgd.ModelConfig(1, 1024, 8, 2, 128, 128, 128, rgd.DTYPE_BF16, 1e-5, 500000.0, 512), top, layers, 9)
+    w = lambda *s: t.randn(*s, generator=g, device="cuda").to(bf)  # noqa: E731
+    R, P, n = 9, 150, 9 * 8 * 128
+    q, k, v = w(R, 8 * 128), w(1, 2, P, 128), w(1, 2, 3, 128, 64)
+    tk, tv = w(R, 2, 16, 128), w(R, 2, 128, 16)
+    pages = t.arange(R, device="cuda", dtype=t.int32).view(R, 1)
+
+    def run(q, out):
+        rgd.kernel_attention(m, q, [0] * R, [P - r for r in range(R)], k, v, 1, P, tk, tv, 16, pages, 1, 7, out)
+        t.cuda.synchronize()
+        return out
+    want = run(q, t.empty_like(q))
+    off = t.empty(n + 8, dtype=bf, device="cuda")[1:n + 1].view(R, 8 * 128)
+    off.copy_(q)
+    both = q.clone()
+    assert t.isfinite(want.float()).all()
+    assert t.equal(run(off, t.empty_like(q)), want) and t.equal(run(both, both), want)
+
+
+@pytest.mark.parametrize("V", [4, 1028, 8196])
+def test_prompt_logits_at_any_float_offset(rgd, V):
+    """The first draw copies the prompts' logits 16 bytes at a time where source and tap allow it, else 4."""
+    t = torch()
+    g = t.Generator(device="cuda").manual_seed(V)
+    top, layers = _world(t, V, 1024, 128, 8, 2, V)
+    m = rgd.Model(rgd.ModelConfig(1, 1024, 8, 2, 128, 128, V, rgd.DTYPE_BF16, 1e-5, 500000.0, 64), top, layers, 6)
+    z = lambda *s: t.zeros(s, dtype=t.bfloat16, device="cuda")  # noqa: E731
+    logits = t.randn(2, V, generator=g, device="cuda")
+    got = []
+    for src, dst in ((0, 0), (1, 0), (0, 1), (3, 2)):
+        kv = rgd.KV(m, 2, 16, 6, 16, z(1, 2, 2, 16, 128), z(1, 2, 2, 1, 128, 64), z(1, 6, 2, 16, 128),
+                    z(1, 6, 2, 128, 16))
+        last = t.empty(2 * V + 4, device="cuda")[src:src + 2 * V].view(2, V)
+        last.copy_(logits)
+        tap = t.full((6 * V + 4,), -7.0, device="cuda")
+        out = t.empty(2, 3, 1, dtype=t.int32, device="cuda")
+        rgd.prefill_kv(m, kv, t.zeros(2, 1, dtype=t.int32, device="cuda"), 0, t.empty(2, V, device="cuda"))
+        rgd.sample_continuations(m, kv, last, [0, 1], 3, 1, 1.0, 0.1, t.arange(6, device="cuda"), out,
+                                 logits_tap=tap[dst:dst + 6 * V].view(1, 6, V))
+        t.cuda.synchronize()
+        assert t.equal(tap[dst:dst + 6 * V].view(6, V), logits.repeat_interleave(3, 0))
+        assert bool((tap[:dst] == -7.0).all()) and bool((tap[dst + 6 * V:] == -7.0).all())
+        got.append(out)
+    assert all(t.equal(got[0], o) for o in got)
