@@ -191,10 +191,11 @@ RGD_DEV int select_token(const SampleArgs& a, int r, float mx, float u, float mi
   __syncthreads();
   if (wave == 0) {
     // running sums in chunk order, 64 chunks at a time (nchunks <= 256)
-    float incl[4], off = 0.f;
+    float sum[4], incl[4], off = 0.f;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const float v = wave_inclusive_scan(raw[64 * i + lane]);
+      sum[i] = raw[64 * i + lane];
+      const float v = wave_inclusive_scan(sum[i]);
       incl[i] = v + off;
       off += __shfl(v, 63, 64);
     }
@@ -204,16 +205,17 @@ RGD_DEV int select_token(const SampleArgs& a, int r, float mx, float u, float mi
       const float t = __shfl(incl[i], (a.nchunks - 1) & 63, 64);
       if ((a.nchunks - 1) >> 6 == i) total = t;
     }
+    // first chunk whose running sum passes the target; the last one with weight.
+    // Only chunks with weight count: neighbouring lanes of the scan add in
+    // different orders, so the running sum can rise by an ulp at an empty chunk.
     const float target = u * total;
     int first = 0x7FFFFFFF, last = 0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int c = 64 * i + lane;
-      const float up = __shfl_up(incl[i], 1, 64), before = i ? __shfl(incl[i ? i - 1 : 0], 63, 64) : 0.f;
-      const float prev = lane ? up : before;
-      if (c < a.nchunks) {
-        if (incl[i] > prev) last = c;
-        if (incl[i] > target && prev <= target) first = min(first, c);
+      if (c < a.nchunks && sum[i] > 0.f) {
+        last = c;
+        if (incl[i] > target) first = min(first, c);
       }
     }
 #pragma unroll
@@ -638,6 +640,11 @@ __global__ __launch_bounds__(256) void minp_select_sub_kernel(SampleArgs a) {
     const float u = philox_uniform(a.seeds[r], a.ctr, a.stream);
     const float thr = a.row_thr ? a.row_thr[r] : a.p_min;
     mx = wave_max(mx);
+    // sub-chunks with weight (the scans below round: a lane's first running sum may
+    // pass the previous lane's last one by an ulp without any weight in between)
+    unsigned some = 0u;
+#pragma unroll
+    for (int i = 0; i < kMaxSP; ++i) some |= loc[i] > 0.f ? 1u << i : 0u;
 #pragma unroll
     for (int i = 1; i < kMaxSP; ++i) loc[i] += loc[i - 1];
     const float tl = loc[kMaxSP - 1];
@@ -651,17 +658,14 @@ __global__ __launch_bounds__(256) void minp_select_sub_kernel(SampleArgs a) {
     if (lane == 0) excl = 0.f;
     const float W = __shfl(incl, 63, 64);
     const float target = u * W;
-    // first sub-chunk whose running sum passes the target; the last non-empty one
+    // first sub-chunk with weight whose running sum passes the target; the last with weight
     int jf = 0x7FFFFFFF, jl = -1;
-    float prev = excl;
 #pragma unroll
     for (int i = 0; i < kMaxSP; ++i) {
       const int j = lane * SP + i;
-      if (i < SP && j < nsub) {
-        const float run = excl + loc[i];
-        if (run > prev) jl = j;
-        if (jf == 0x7FFFFFFF && run > target) jf = j;
-        prev = run;
+      if (some >> i & 1u) {  // (masked entries have none)
+        jl = j;
+        if (jf == 0x7FFFFFFF && excl + loc[i] > target) jf = j;
       }
     }
 #pragma unroll
