@@ -337,8 +337,11 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(GemmArgs a) {
 // against 79 us, down projection 41 against 44, LM head 290 against 325; the QKV
 // projection with its 16 steps per split takes 34 against 27 us and stays with
 // the 128-row tiles, as does the O projection, 23 against 20).
+// X goes to LDS in 16-byte copies with 32-bit offsets and Y is stored 16 bytes at
+// a time; rows at other addresses stay with gemm.hip's ordinary loads and stores.
 bool gemm_wide_fits(const GemmArgs& a) {
-  if (a.M <= kWideRows || (long long)a.M * a.ldx * 2 >= (1ll << 31) || (uintptr_t)a.y % 16 || a.ldy % 4 || a.N % 4) return false;
+  if (a.M <= kWideRows || (long long)a.M * a.ldx * 2 >= (1ll << 31)) return false;
+  if ((uintptr_t)a.x % 16 || a.ldx % 8 || (uintptr_t)a.y % 16 || a.ldy % 4 || a.N % 4) return false;
   for (int i = 1; i < a.nseg && a.mode == GEMM_STORE; ++i)
     if (a.seg[i].n0 % kBN) return false;
   return a.M > kBM || a.K / a.splits >= 24 * kStep;

@@ -90,6 +90,24 @@ def test_lm_head_rows_alone_and_together(rgd, R, V):
     assert t.equal(out[:R], rows) and bool((out[R] == -7.0).all())
 
 
+@pytest.mark.parametrize("R,d", [(300, 1024), (130, 2048)])
+def test_lm_head_of_hidden_states_at_any_element(rgd, R, d):
+    """Hidden states at 2-, 8- and 16-byte offsets: the 256-row tiles copy 16-byte pieces of aligned rows only."""
+    t = torch()
+    V = 68
+    top, layers = _world(t, R, d, 128, 1, 1, V)
+    m = rgd.Model(rgd.ModelConfig(1, d, 1, 1, 128, 128, V, rgd.DTYPE_BF16, 1e-5, 500000.0, 64), top, layers, R)
+    h = t.randn(R, d, generator=t.Generator(device="cuda").manual_seed(R), device="cuda").bfloat16()
+    want, got = t.empty(R, V, device="cuda"), t.empty(R, V, device="cuda")
+    rgd.kernel_lm_head(m, h, want)
+    for off in (1, 4, 8):
+        at = t.empty(R * d + 8, dtype=t.bfloat16, device="cuda")[off:off + R * d].view(R, d)
+        at.copy_(h)
+        rgd.kernel_lm_head(m, at, got.zero_())
+        t.cuda.synchronize()
+        assert t.equal(got, want), off
+
+
 @pytest.mark.parametrize("heads,kv_heads", [(32, 8), (6, 2)])
 def test_tail_attention_of_many_rows(rgd, heads, kv_heads):
     """Rows of a batch large enough for one-wave tail workgroups against the same rows few at a time (four waves):
