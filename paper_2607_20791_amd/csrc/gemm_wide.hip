@@ -34,12 +34,17 @@ constexpr int kXBytes = kBM * kStep * 2;  // X of one 64-k step in LDS
 
 // 1 KiB from global memory to LDS, 16 bytes a lane: base + off (per lane) +
 // OFF to lds + DST + OFF + 16 * lane.  No register is written; the compiler does not count it.
+// (m0 is reserved: the compiler never holds a value there across statements, which
+// its warning is about, but orders its own uses of m0 by the clobber.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 template <int DST, int OFF>
 RGD_DEV void dma16(const char* base, uint32_t off, uint32_t lds) {
   asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:%4" ::"v"(off), "s"(base),
                "s"(lds), "n"(DST), "n"(OFF)
-               : "scc");
+               : "m0", "scc");
 }
+#pragma clang diagnostic pop
 template <int A, int B, typename F>
 RGD_DEV void static_for(F&& f) {
   if constexpr (A < B) {
