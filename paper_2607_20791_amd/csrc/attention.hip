@@ -510,9 +510,12 @@ __global__ __launch_bounds__(NW * 64) void attn_prefix_kernel(AttnArgs a, bf16_t
 constexpr int kChunk = 256;      // positions per prefix split and per tail block
 constexpr int kMaxSplits = 40;
 
-// 8 consecutive elements starting at p (16-byte aligned)
+// four floats of a caller's K or V, which need not be aligned to 16 bytes
+typedef f32x4 f32x4_any __attribute__((aligned(4)));
+
+// 8 consecutive elements starting at p
 RGD_DEV void load8(const float* p, float* out) {
-  const f32x4 a = *(const f32x4*)p, b = *(const f32x4*)(p + 4);
+  const f32x4 a = *(const f32x4_any*)p, b = *(const f32x4_any*)(p + 4);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     out[i] = a[i];
@@ -532,7 +535,7 @@ RGD_DEV void f32_scores(const float (&qs)[8][D], float (&sc)[8][kChunk], int n, 
     const float* kr = k_row(min(p, n - 1));
     f32x4 k[NV];
 #pragma unroll
-    for (int i = 0; i < NV; ++i) k[i] = *(const f32x4*)(kr + min(j * 4 + i * 16, D - 4));
+    for (int i = 0; i < NV; ++i) k[i] = *(const f32x4_any*)(kr + min(j * 4 + i * 16, D - 4));
 #pragma unroll
     for (int h = 0; h < 8; ++h) {
       if (h >= G) break;

@@ -66,3 +66,28 @@ def test_attention_f32_heads(rgd, D, hq, hk):
                            (70, 600, None)]:
         err = _attn_case(rgd, w, m, 3, 2, P, tail, plens=plens, seed=P + tail)
         assert err.max() <= 1e-5, (P, tail, err.max())
+
+
+@pytest.mark.parametrize("off", [1, 2])
+def test_attention_f32_caches_at_any_float(rgd, off):
+    """K and V buffers that start 4 and 8 bytes past a 16-byte boundary give the bits of aligned ones."""
+    t = torch()
+    w = synth.scaled(BASE, head_dim=32, n_heads=4, n_kv_heads=2, d_model=64, ffn=64, vocab=64)
+    m = _model(rgd, w, max_rows=8, max_pos=2048)
+    g = t.Generator(device="cuda").manual_seed(off)
+    rnd = lambda *s: t.randn(s, generator=g, device="cuda")  # noqa: E731
+    R, P, tail, n = 6, 300, 37, 3
+    q, bufs = rnd(R, 4 * 32), [rnd(1, 2, P, 32), rnd(1, 2, 5, 32, 64), rnd(R * n, 2, 16, 32), rnd(R * n, 2, 32, 16)]
+    pages = t.arange(R * n, device="cuda", dtype=t.int32).view(R, n)
+
+    def run(k, v, tk, tv):
+        out = t.empty(R, 4 * 32, device="cuda")
+        rgd.kernel_attention(m, q, [0] * R, [P - r for r in range(R)], k, v, 1, P, tk, tv, 16, pages, n, tail, out)
+        t.cuda.synchronize()
+        return out
+
+    def moved(x):
+        y = t.empty(x.numel() + 4, device="cuda")[off:off + x.numel()].view(x.shape)
+        return y.copy_(x)
+    want = run(*bufs)
+    assert t.isfinite(want).all() and t.equal(run(*map(moved, bufs)), want)
