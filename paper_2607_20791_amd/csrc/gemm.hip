@@ -302,9 +302,9 @@ __global__ __launch_bounds__(NW * 64) void gemm_bf16_kernel(GemmArgs a) {
   }
 }
 
-// Row tiles per workgroup follow M (16, 32, 64 or 128 rows; up to 256 rows, or
-// where the wide tiles do not apply, several 128-row blocks, whose weight reads
-// then largely hit in L2); the
+// Row tiles per workgroup follow M (16, 32, 64 or 128 rows; above, where the wide
+// tiles of gemm_wide.hip do not fit or do not win, several 128-row blocks, whose
+// weight reads then largely hit in L2); the
 // 128-row tile stages X two 64-k steps at a time (LDS; one step per barrier
 // measured 13-18% slower for the LM head and the projections at 128 rows).
 // The tile height never changes a row's arithmetic.
@@ -351,12 +351,11 @@ int gemm_groups(int mode, int N) {
 // * up to 64 rows: split-K projections <1, 8, 4, 2>, SwiGLU <1, 4, 4, 4>;
 // * 65-128 rows (one 128-row tile): both <1, 8, 4> (128 columns per
 //   workgroup for split-K, 64 output features for SwiGLU);
-// * 129-256 rows, split-K projections with fewer than 24 steps per split (the
-//   other GEMMs of more rows run the wide tiles of gemm_wide.hip): <2, 8, 4>
-//   (256 columns per workgroup: the two 128-row blocks of a column group then
-//   stream twice the weights per X stage they load), except where a split
-//   covers at most 8 steps (the O projection), which keeps one panel per wave
-//   with two steps in flight <1, 8, 2>;
+// * more rows, where the wide tiles of gemm_wide.hip are not faster: both <2, 8, 4>
+//   (256 columns or 128 features per workgroup: the two 128-row blocks of a column
+//   group then stream twice the weights per X stage they load), except projections
+//   whose splits cover at most 8 steps (the O projection), which keep one panel
+//   per wave with two steps in flight <1, 8, 2>;
 // * the LM head <4, 8, 2> (512 columns per workgroup: the X rows every
 //   workgroup streams through LDS cost half as much per weight byte).
 // A row's arithmetic is the same under every shape (same k order, same
@@ -388,7 +387,7 @@ hipError_t gemm_bf16(const GemmArgs& a, hipStream_t s) {
   const int g = gemm_groups(a.mode, a.N);
   if (a.mode == GEMM_LOGITS && a.ntiles != g) return hipErrorInvalidValue;
   if (a.mode != GEMM_STORE && a.splits != 1) return hipErrorInvalidValue;
-  if (gemm_wide_fits(a)) return gemm_wide(a, s);
+  if (gemm_wide_fits(a) && (a.summed || gemm_wide_wins(a))) return gemm_wide(a, s);
   if (a.summed) return hipErrorInvalidValue;
   switch (a.mode) {
     case GEMM_STORE:

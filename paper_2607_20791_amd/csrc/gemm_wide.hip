@@ -22,6 +22,8 @@
 // 64 x 64 (LDS traffic 176 instead of 144 KiB a step), 256-column tiles on two
 // LDS slots, a fourth weight slot and a wave that touches the weights ahead
 // were no faster.
+#include <algorithm>
+
 #include "gemm_common.hpp"
 #include "kernels.hpp"
 
@@ -334,38 +336,62 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(GemmArgs a) {
 
 }  // namespace
 
-// Rows and shapes the wide tiles are used for.  Above 256 rows always (one
-// 8B-class layer's chunk of 2048 rows: SwiGLU 392 against 506 us with the
-// 128-row tiles of gemm.hip, the split-K projections, which here add their
-// splits themselves, 393 against 591 us); from 129 to 256 rows where a
-// workgroup has 24 or more steps to run (in a 256-row decode step SwiGLU 69
-// against 79 us, down projection 41 against 44, LM head 290 against 325; the QKV
-// projection with its 16 steps per split takes 34 against 27 us and stays with
-// the 128-row tiles, as does the O projection, 23 against 20).
-// X goes to LDS in 16-byte copies with 32-bit offsets and Y is stored 16 bytes at
-// a time; rows at other addresses stay with gemm.hip's ordinary loads and stores.
+// Shapes that the wide tiles take.  X goes to LDS in 16-byte copies with 32-bit
+// offsets and Y is stored 16 bytes at a time; rows at other addresses stay with
+// gemm.hip's ordinary loads and stores.
 bool gemm_wide_fits(const GemmArgs& a) {
   if (a.M <= kWideRows || (long long)a.M * a.ldx * 2 >= (1ll << 31)) return false;
   if ((uintptr_t)a.x % 16 || a.ldx % 8 || (uintptr_t)a.y % 16 || a.ldy % 4 || a.N % 4) return false;
   for (int i = 1; i < a.nseg && a.mode == GEMM_STORE; ++i)
     if (a.seg[i].n0 % kBN) return false;
-  return a.M > kBM || a.K / a.splits >= 24 * kStep;
+  return true;
+}
+
+static long long rounds(long long workgroups) { return (workgroups + 255) / 256; }
+
+// Whether they are faster than the 128-row tiles of gemm.hip.  Both run in rounds
+// of 256 workgroups (one per CU), so the rounds decide, with the time of a wide
+// workgroup over that of one of the others.  Measured with cold weights (us, 128-row
+// tiles / wide):
+// * LM head, 1.4 (K 1024) to 1.6 (K 4096) times: vocabulary 128256, K 4096, 129-256
+//   rows (2 rounds against 1) 309 / 275, 257-384 (3 / 2) 437 / 467, 513-640 (5 / 3)
+//   707 / 693; vocabulary 32768, 129-512 rows (1 / 1) 135 / 160-200; 513 (2 / 1) 250 / 199.
+// * SwiGLU, 0.75 times: 4096 x 14336, 256 rows (1 / 1) 74 / 67, 512 (2 / 2) 138 / 110;
+//   3072 x 10752, 257-384 rows (1 / 2) 62 / 76; 1024 x 3584 (16 steps) 24 / 14.
+// * Projections from 129 to 256 rows where a split has 24 or more steps to run (in a
+//   256-row decode step the down projection 41 against 44 us; the QKV projection
+//   with its 16 steps per split takes 34 against 27 there, the O projection 23
+//   against 20).
+// * Projections above 256 rows, 0.85 times a 256-column workgroup: K 4096 QKV 257-384
+//   rows (2 / 2) 46 / 41, 513-640 (2 / 3) 50 / 57.  Splits of at most 8 steps, whose 128-row
+//   workgroups are 128 columns wide and share a CU: K 2048 QKV 257-384 rows 20 / 21,
+//   448 23 / 21; K 1024 QKV 512 rows 9.3 / 11.2, 1024 14.0 / 12.6.
+bool gemm_wide_wins(const GemmArgs& a) {
+  const long long M = a.M, nb = (M + 127) / 128, wb = (M + kBM - 1) / kBM;
+  auto cols = [&](int c) { return (long long)(a.N + c - 1) / c; };
+  if (a.mode == GEMM_LOGITS) return (26600 + a.K) * rounds(cols(512) * wb) <= 20000 * rounds(cols(512) * nb);
+  if (a.mode == GEMM_SILU) return 3 * rounds(cols(64) * wb) <= 4 * rounds(cols(128) * nb);
+  const int steps = a.K / kStep / a.splits;
+  if (M <= kBM) return steps >= 24;
+  const long long w = rounds(cols(128) * wb * a.splits);
+  if (steps > 8) return 17 * w <= 20 * rounds(cols(256) * nb * a.splits);
+  return 6 * 256 * w <= 5 * std::max(256ll, cols(128) * nb * a.splits);
 }
 
 // Whether a projection's workgroups run their splits one after the other and
 // add them, instead of one workgroup per split writing a partial output that
 // the consumer adds: the fewer, longer workgroups against the partials' traffic.
-// Costs in units of 0.1 us: 8.5 for a 64-k step of a tile, 30 for the start and
-// end of a workgroup, rounds of 256 workgroups, and the partials written and
-// read at 4 TB/s.  Measured (us, one after the other / partials, without their
-// read): 1024 rows QKV 62 / 69, O 61 / 64, down 177 / 131; 2048 rows 120 / 134,
-// 72 / 131, 201 / 280.
+// Costs in units of 0.01 us: 70 for a 64-k step of a tile and 700 for the start and
+// end of a workgroup that runs all splits, 75 and 300 for one of a single split,
+// rounds of 256 workgroups, and the partials written and read at 4.4 TB/s.
+// Measured (us, one after the other / partials, with their read): K 1024 QKV 1024 rows
+// 20.7 / 18.9, 2048 22.2 / 35.2; K 2048 QKV 385 rows 32.6 / 30.4, 512 33.1 / 34.6; K
+// 4096 QKV 1024 rows 57 / 90, O 59 / 95; down (K 14336) 1024 167 / 160, 2048 194 / 347.
 bool gemm_sums_splits(const GemmArgs& a) {
   if (a.mode != GEMM_STORE || a.splits == 1 || a.M <= kBM || !gemm_wide_fits(a)) return false;
   const long long tiles = (long long)((a.N + kBN - 1) / kBN) * ((a.M + kBM - 1) / kBM), nst = a.K / kStep;
-  const long long one = (tiles + 255) / 256 * (85 * nst + 300);
-  const long long parts = (tiles * a.splits + 255) / 256 * (85 * nst / a.splits + 300) +
-                          (long long)a.splits * a.M * a.N * 8 / 40000;
+  const long long one = rounds(tiles) * (70 * nst + 700);
+  const long long parts = rounds(tiles * a.splits) * (75 * nst / a.splits + 300) + (long long)a.splits * a.M * a.N * 8 / 44000;
   return one < parts;
 }
 

@@ -46,7 +46,8 @@ int gemm_groups(int mode, int N);   // workgroups along N for a mode
 hipError_t gemm_bf16(const GemmArgs& a, hipStream_t s);
 // many rows (more than kWideRows): gemm_wide.hip
 constexpr int kWideRows = 128;
-bool gemm_wide_fits(const GemmArgs& a);
+bool gemm_wide_fits(const GemmArgs& a);   // they can run this
+bool gemm_wide_wins(const GemmArgs& a);   // and are faster than the 128-row tiles
 bool gemm_sums_splits(const GemmArgs& a);
 hipError_t gemm_wide(const GemmArgs& a, hipStream_t s);
 hipError_t gemm_f32(const GemmArgs& a, hipStream_t s);

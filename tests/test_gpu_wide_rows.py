@@ -45,19 +45,25 @@ def _prefill(rgd, t, world, dims, tokens, max_rows):
     return last, kv.prefix_k, kv.prefix_v
 
 
-# (d, ffn, heads, kv heads, vocab), prompts, tokens, max_rows of the wide run:
-# one partial tile past 256 rows; 2 + 1 tiles with an odd step count per split
-# (88 steps over 8 splits) and an uneven split (22 steps over 4); chunks whose
-# projections add their splits themselves (2100 rows, a 52-row last tile), with
-# four and with eight heads per KV head; rows of several prompts in one chunk,
-# with prefix splits of one and of three 64-position tiles.  The wide runs of all
-# but the first walk over the prefix splits in the attention, the narrow ones
-# attend split by split.  The last two: last rows that go through the LM head
-# prompt by prompt's chunk (held back, in two lots for 70 prompts) and in place.
+# (d, ffn, heads, kv heads, vocab), prompts, tokens, max_rows of the wide run.
+# SwiGLU runs 256-row tiles in every chunk of more than 128 rows but that of 513 (one
+# partial tile past 256 rows; 2 + 1 tiles and more).  The projections do where there are
+# enough workgroups or steps: an uneven split (88 steps over 16 at 513 rows, 22 over
+# 4 at 1300), the three segments of QKV at 1000.  They add their splits themselves
+# in the chunks of 2100 (a 52-row last tile; 22 steps over 4 and 56 over 8; four and
+# eight heads per KV head), 2600 and, at d = 4096, 690 rows.  Rows of several
+# prompts in one chunk, with prefix splits of one and of three 64-position tiles.
+# The wide runs walk over the prefix splits in the attention, those of few rows
+# attend split by split, except in the first case (20 workgroups), the last
+# chunk of the second and the chunk of 5 x 30 tokens (10), which do not walk, and in the
+# chunk of 64 one-token prompts, which walks in both.  The last two cases: last rows that go
+# through the LM head prompt by prompt's chunk (held back, in two lots for 70
+# prompts) and in place.
 CASES = [((1024, 2816, 8, 4, 512), 1, 257, 300), ((1024, 5632, 8, 2, 512), 1, 700, 513),
          ((1024, 1408, 8, 2, 512), 1, 600, 600), ((1024, 3584, 8, 2, 512), 1, 2100, 2100),
          ((1024, 1408, 8, 1, 512), 1, 2100, 2100),
          ((4096, 1152, 32, 8, 512), 3, 230, 700), ((1024, 1408, 8, 8, 512), 2, 1300, 2600),
+         ((1024, 1408, 8, 2, 512), 1, 1300, 1300), ((1024, 1408, 8, 2, 512), 1, 1000, 1000),
          ((1024, 128, 8, 2, 512), 5, 30, 150), ((1024, 128, 8, 2, 512), 70, 1, 70)]
 
 
@@ -90,11 +96,29 @@ def test_lm_head_rows_alone_and_together(rgd, R, V):
     assert t.equal(out[:R], rows) and bool((out[R] == -7.0).all())
 
 
-@pytest.mark.parametrize("R,d", [(300, 1024), (130, 2048)])
-def test_lm_head_of_hidden_states_at_any_element(rgd, R, d):
+# vocabularies at which the 256-row tiles take these rows (two rounds of 128-row workgroups or more
+# against one): they end inside a 64-column group, at its end and inside a
+# 512-column workgroup; two steps of 64 k, and 16; rows of one tile, of a partial second
+# and of a partial third
+@pytest.mark.parametrize("R,V,d", [(129, 66308, 128), (200, 66112, 1024), (256, 131076, 128), (257, 44100, 1024),
+                                   (300, 65476, 384), (512, 44032, 128), (513, 33100, 1024)])
+def test_lm_head_on_wide_tiles(rgd, R, V, d):
+    t = torch()
+    top, layers = _world(t, R, d, 128, 1, 1, V)
+    m = rgd.Model(rgd.ModelConfig(1, d, 1, 1, 128, 128, V, rgd.DTYPE_BF16, 1e-5, 500000.0, 64), top, layers, R)
+    h = t.randn(R, d, generator=t.Generator(device="cuda").manual_seed(R), device="cuda").bfloat16()
+    out, rows = t.full((R + 1, V), -7.0, device="cuda"), t.empty(R, V, device="cuda")
+    rgd.kernel_lm_head(m, h, out[:R])
+    for r in range(0, R, 64):
+        rgd.kernel_lm_head(m, h[r:r + 64], rows[r:r + 64])
+    t.cuda.synchronize()
+    assert t.equal(out[:R], rows) and bool((out[R] == -7.0).all())
+
+
+@pytest.mark.parametrize("R,d,V", [(300, 1024, 65476), (130, 2048, 66308)])
+def test_lm_head_of_hidden_states_at_any_element(rgd, R, d, V):
     """Hidden states at 2-, 8- and 16-byte offsets: the 256-row tiles copy 16-byte pieces of aligned rows only."""
     t = torch()
-    V = 68
     top, layers = _world(t, R, d, 128, 1, 1, V)
     m = rgd.Model(rgd.ModelConfig(1, d, 1, 1, 128, 128, V, rgd.DTYPE_BF16, 1e-5, 500000.0, 64), top, layers, R)
     h = t.randn(R, d, generator=t.Generator(device="cuda").manual_seed(R), device="cuda").bfloat16()
