@@ -332,19 +332,35 @@ struct RowArrays {
 // Whether a prefill chunk's attention walks over the prefix splits, one workgroup
 // per (row block, KV head), instead of one workgroup per split whose partials
 // the tail kernel merges for every row.  A walk writes no partials (a 2048-row
-// chunk at 4096 positions: 210 MB) and most rows need no tail kernel, but it leaves the
-// chip idle when there are few row blocks, which only short prompts make up for.
-// Measured (8 KV heads, whole prefill of one layer, us, walk / splits): 2048-row chunks
-// of a 4096-token prompt 2385 / 2720, 1024 rows of 1024 tokens 858 / 932, 512
-// rows 567 / 581; with 64 workgroups 256-row chunks of eight 1000-token prompts
-// 8352 / 8522, of a 4096-token prompt 4353 / 4083.
+// chunk at 4096 positions: 210 MB) and most rows need no tail kernel, but it
+// runs its tiles one after the other on few CUs.  Costs in units of 0.01 us, fitted
+// to 350 measured chunks (1 to 8 KV heads, 1 to 8 query heads each, 64-2048 rows, up
+// to 8192 positions; the side taken is 0.1% slower than the better one on average, 6%
+// at worst): 100 per 64-position tile and round of 256 workgroups, 200 per round of
+// split workgroups and per split that a walk closes, then the tail kernel with
+// the partials that its four waves load per row and KV head, and its workgroups.
+// Attention stage, us, split / walk, one prompt, 32 query and 8 KV heads: 256 rows
+// at 1024 positions 57 / 66, 512 rows 101 / 71 and at 8192 positions 155 / 185, 1024
+// rows at 8192 303 / 212; 8 and 2 heads: 512 rows at 1024 35 / 58, 2048 at 4096 175 / 137.
 void plan_walk(const rgd_model* m, const rgd_kv* kv, HostRows& h) {
   h.walk = false;
   h.left.clear();
-  const long long wgs = (long long)h.blocks.size() * m->cfg.n_kv_heads;
-  if (!m->bf16 || wgs < 32 || (wgs < 128 && h.maxplen > 1024)) return;
-  h.walk = true;
+  if (!m->bf16) return;
   const int len = kv->layer(0).split_len;
+  const long long R = (long long)h.plen.size(), Hkv = m->cfg.n_kv_heads, Hq = m->cfg.n_heads;
+  const long long S = cdiv(h.maxplen, len);
+  long long walk = 270 + 120 * R * Hkv / 1000;
+  long long split = (6 * std::max(4 * Hkv, Hq) + 15 * Hq) * R * S / 1000 + 400 * R * Hkv / 1000;
+  for (size_t b0 = 0; b0 < h.blocks.size(); b0 += kAttnInlineBlocks) {  // one launch of the kernel
+    const size_t nb = std::min<size_t>(kAttnInlineBlocks, h.blocks.size() - b0);
+    int longest = 0;
+    for (size_t i = 0; i < nb; ++i) longest = std::max(longest, h.blocks[b0 + i].w);
+    const long long tiles = cdiv(longest, 64), ns = cdiv(longest, len);
+    walk += cdiv((long long)nb * Hkv, 256) * (100 * tiles + 200 * ns);
+    split += cdiv((long long)nb * Hkv * ns, 256) * (100 * std::min<long long>(len / 64, tiles) + 200);
+  }
+  if (walk >= split) return;
+  h.walk = true;
   for (size_t r = 0; r < h.plen.size(); ++r)
     if (prefix_part_end(h.plen[r], len) != h.plen[r]) h.left.push_back((int)r);
 }
