@@ -49,15 +49,18 @@ def log(*a):
 
 def measured_traffic(name="lm_head_8b_layer_p8192_traffic.md"):
     """HBM bytes per launch from the committed counter summary, or None when
-    the kernel source changed since the counters were taken."""
+    the kernel's source (the files the summary lists, headers included) changed
+    since the counters were taken."""
     import hashlib
     import re
     try:
         text = open(os.path.join(ROOT, "profiles", name)).read()
         block = re.search(r"```traffic\n(.*?)```", text, re.S).group(1)
         kv = dict(line.split("=", 1) for line in block.strip().splitlines())
-        src = open(os.path.join(ROOT, kv["source"]), "rb").read()
-        if hashlib.sha256(src).hexdigest() != kv["sha256"]:
+        src = hashlib.sha256()
+        for f in kv["sources"].split():
+            src.update(open(os.path.join(ROOT, f), "rb").read())
+        if src.hexdigest() != kv["sha256"]:
             return None
         return int(kv["bytes_per_launch"])
     except Exception:  # pragma: no cover

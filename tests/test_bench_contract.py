@@ -36,22 +36,34 @@ def test_traffic_follows_the_kernel_source_hash(tmp_path):
     b = _bench()
     name = "lm_head_8b_layer_p8192_traffic.md"
     kv = _traffic_block(name)
-    src = open(os.path.join(ROOT, kv["source"]), "rb").read()
-    current = hashlib.sha256(src).hexdigest() == kv["sha256"]
+    files = kv["sources"].split()
+    # the kernel and the headers that hold its helpers
+    assert {os.path.basename(f) for f in files} >= {"gemm.hip", "gemm_common.hpp", "common.hpp"}
+    src = [open(os.path.join(ROOT, f), "rb").read() for f in files]
+    current = hashlib.sha256(b"".join(src)).hexdigest() == kv["sha256"]
     got = b.measured_traffic(name)
     if current:
         assert got == int(kv["bytes_per_launch"]) and got > 0
     else:
         assert got is None
-    # a summary whose recorded hash does not match its source gives null
-    text = open(os.path.join(ROOT, "profiles", name)).read().replace(kv["sha256"], "0" * 64)
+    # a summary whose recorded hash does not match its sources gives null
+    summary = open(os.path.join(ROOT, "profiles", name)).read()
     os.makedirs(tmp_path / "profiles")
-    (tmp_path / "profiles" / name).write_text(text)
-    copied = tmp_path / kv["source"]
-    os.makedirs(copied.parent)
-    copied.write_bytes(src)
+    for f, data in zip(files, src):
+        os.makedirs((tmp_path / f).parent, exist_ok=True)
+        (tmp_path / f).write_bytes(data)
     b.ROOT = str(tmp_path)
-    assert b.measured_traffic(name) is None
-    # and the untouched summary beside the same source reads as before
-    (tmp_path / "profiles" / name).write_text(open(os.path.join(ROOT, "profiles", name)).read())
-    assert b.measured_traffic(name) == got
+
+    def traffic(sha):
+        (tmp_path / "profiles" / name).write_text(summary.replace(kv["sha256"], sha))
+        return b.measured_traffic(name)
+    assert traffic("0" * 64) is None
+    # and the untouched summary beside the same sources reads as before
+    assert traffic(kv["sha256"]) == got
+    # a change of any one of the files makes the figure stale
+    now = hashlib.sha256(b"".join(src)).hexdigest()
+    for f, data in zip(files, src):
+        (tmp_path / f).write_bytes(data + b"\n")
+        assert traffic(now) is None
+        (tmp_path / f).write_bytes(data)
+    assert traffic(now) == int(kv["bytes_per_launch"])
