@@ -61,7 +61,9 @@ constexpr float kNoRef = -3.0e38f;
 // sum of their weights relative to it, the outputs summed so far are scaled by a
 // and the next split's normalised output enters with weight b.  The kernel that
 // walks over all splits and the merge kernel share this step (and round a
-// split's output to bf16 before it), so both give the same bits.
+// split's output to bf16 before it), so both give the same bits.  Only a split with no
+// visible position (weight sum 0) is left out: a weight sum that is not a number,
+// from a NaN among the scores, enters like any other and makes the output NaN.
 RGD_DEV void merge_step(float& mx, float& den, float lse, float& a, float& b) {
   const float nm = fmaxf(mx, lse);
   a = mx == -INFINITY ? 0.f : __expf(mx - nm);
@@ -401,7 +403,7 @@ __global__ __launch_bounds__(NW * 64) void attn_prefix_kernel(AttnArgs a, bf16_t
 #pragma unroll
     for (int nt = 0; nt < NQ; ++nt) {
       const float lt = lacc[nt][0];
-      const bool some = lt > 0.f;
+      const bool some = lt != 0.f;
       const float inv = some ? 1.0f / lt : 0.f;
       float wa = 1.f, wb = 0.f;
       if (some) merge_step(wmx[nt], wden[nt], (m[nt] + __log2f(lt)) * kLn2, wa, wb);
@@ -494,7 +496,7 @@ __global__ __launch_bounds__(NW * 64) void attn_prefix_kernel(AttnArgs a, bf16_t
       for (int dt = 0; dt < 8; ++dt)
         *(u32x2*)(po + dt * 16 + grp * 4) = u32x2{pack2(o[dt][nt][0] * inv, o[dt][nt][1] * inv),
                                                   pack2(o[dt][nt][2] * inv, o[dt][nt][3] * inv)};
-      if (grp == 0) a.part_lse[idx] = lt > 0.f ? (m[nt] + __log2f(lt)) * kLn2 : -INFINITY;
+      if (grp == 0) a.part_lse[idx] = lt != 0.f ? (m[nt] + __log2f(lt)) * kLn2 : -INFINITY;
     }
   }
 }

@@ -1,0 +1,78 @@
+"""A NaN among a prompt's resident keys reaches every row that sees it.
+
+The split partials of bf16 attention are merged by log-sum-exp; a partial that is
+not a number must not be taken for an empty one, or a damaged prompt KV would
+give finite logits and the non-finite check on them would stay silent."""
+import pytest
+
+from tests.gpu_common import torch
+
+pytestmark = pytest.mark.gpu
+HQ, HK, D = 8, 2, 128
+
+
+@pytest.fixture(scope="module")
+def rgd():
+    import paper_2607_20791_amd as m
+    return m
+
+
+def _world(t, heads, kv_heads, V):
+    g = t.Generator(device="cuda").manual_seed(7)
+    w = lambda *s: (t.randn(*s, generator=g, device="cuda") * 0.05).bfloat16()  # noqa: E731
+    one = t.ones(128, device="cuda")
+    L = {"wq": w(heads * D, 128), "wk": w(kv_heads * D, 128), "wv": w(kv_heads * D, 128), "wo": w(128, heads * D),
+         "w_gate": w(128, 128), "w_up": w(128, 128), "w_down": w(128, 128), "attn_norm": one, "ffn_norm": one}
+    return {"embed": w(V, 128), "final_norm": one, "lm_head": w(V, 128)}, [L]
+
+
+@pytest.mark.parametrize("splits", [1, 3, 11])
+@pytest.mark.parametrize("bad", [0, 300, 699])
+def test_attention(rgd, splits, bad):
+    """Rows that see the position: NaN in the heads of its KV head, as in plain softmax; nothing else changes."""
+    t = torch()
+    top, layers = _world(t, HQ, HK, 128)
+    R, P, tail = 6, 700, 20
+    m = rgd.Model(rgd.ModelConfig(1, 128, HQ, HK, D, 128, 128, rgd.DTYPE_BF16, 1e-5, 500000.0, 1024), top, layers, R)
+    g = t.Generator(device="cuda").manual_seed(splits)
+    w = lambda *s: t.randn(*s, generator=g, device="cuda").bfloat16()  # noqa: E731
+    q, k, v, tk, tv = w(R, HQ * D), w(1, HK, P, D), w(1, HK, 11, D, 64), w(2 * R, HK, 16, D), w(2 * R, HK, D, 16)
+    pages = t.arange(2 * R, device="cuda", dtype=t.int32).view(R, 2)
+    plen = [700, 301, 300, 128, 64, 1]
+
+    def run():
+        out = t.empty(R, HQ * D, dtype=t.bfloat16, device="cuda")
+        rgd.kernel_attention(m, q, [0] * R, plen, k, v, 1, P, tk, tv, 16, pages, 2, tail, out, splits=splits)
+        t.cuda.synchronize()
+        return out.view(R, HK, HQ // HK * D)
+    good = run()
+    k[0, 1, bad, 5] = float("nan")
+    got = run()
+    assert t.isfinite(good.float()).all()
+    for r in range(R):
+        assert t.equal(got[r, 0], good[r, 0])
+        if plen[r] > bad:
+            assert t.isnan(got[r, 1]).all(), (r, plen[r])
+        else:
+            assert t.equal(got[r, 1], good[r, 1]), (r, plen[r])
+
+
+@pytest.mark.parametrize("max_rows", [64, 1000])
+def test_prefill_over_a_resident_prefix(rgd, max_rows):
+    """Chunks attended split by split and (1000 rows) in a walk over the splits."""
+    t = torch()
+    n0, n, V = 100, 1000, 256
+    top, layers = _world(t, 8, 8, V)
+    m = rgd.Model(rgd.ModelConfig(1, 128, 8, 8, D, 128, V, rgd.DTYPE_BF16, 1e-5, 500000.0, n0 + n), top, layers, max_rows)
+    z = lambda *s: t.zeros(s, dtype=t.bfloat16, device="cuda")  # noqa: E731
+    pk = z(1, 1, 8, n0 + n, D)
+    kv = rgd.KV(m, 1, n0 + n, 0, 16, pk, z(1, 1, 8, (n0 + n + 63) // 64, D, 64), z(1, 1, 8, 16, D), z(1, 1, 8, D, 16))
+    tokens = (t.arange(n, device="cuda", dtype=t.int32) * 37 % V).view(1, n)
+    last = t.empty(1, V, device="cuda")
+    for bad in (False, True):
+        if bad:
+            pk[0, 0, 3, 50, 9] = float("nan")
+        kv.set_prefix_len(0, n0)
+        rgd.prefill_kv(m, kv, tokens, n0, last)
+        t.cuda.synchronize()
+        assert bool(t.isnan(last).all() if bad else t.isfinite(last).all())
