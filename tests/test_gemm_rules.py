@@ -48,7 +48,7 @@ def _side(rules, a):
     # LM head: one round of 128-row workgroups beats one of 256-row ones, and three beat two at K = 4096
     (LOGITS, 32000, 4096, 1, 130, "narrow"), (LOGITS, 32000, 4096, 1, 256, "narrow"), (LOGITS, 65536, 2048, 1, 256, "narrow"),
     (LOGITS, 32000, 4096, 1, 512, "narrow"), (LOGITS, 32000, 4096, 1, 600, "wide"), (LOGITS, 65536, 4096, 1, 257, "wide"),
-    (LOGITS, 66048, 1024, 1, 130, "wide"), (LOGITS, 128256, 1024, 1, 130, "wide"), (LOGITS, 128256, 4096, 1, 256, "wide"),
+    (LOGITS, 66308, 128, 1, 130, "wide"), (LOGITS, 65476, 1024, 1, 300, "wide"), (LOGITS, 66048, 1024, 1, 130, "wide"), (LOGITS, 128256, 1024, 1, 130, "wide"), (LOGITS, 128256, 4096, 1, 256, "wide"),
     (LOGITS, 128256, 4096, 1, 257, "narrow"), (LOGITS, 128256, 4096, 1, 400, "wide"), (LOGITS, 128256, 4096, 1, 128, "narrow"),
     # SwiGLU: a second round for 257 to 384 rows does not pay
     (SILU, 3584, 1024, 1, 130, "wide"), (SILU, 14336, 4096, 1, 256, "wide"), (SILU, 14336, 4096, 1, 300, "wide"),

@@ -132,6 +132,39 @@ def test_lm_head_of_hidden_states_at_any_element(rgd, R, d, V):
         assert t.equal(got, want), off
 
 
+@pytest.mark.parametrize("B,d,V", [(130, 128, 66308), (300, 1024, 65476)])
+def test_probe_of_many_prompts(rgd, B, d, V):
+    """Probe steps whose argmax comes from the 256-row tiles' keys (partial last row tile, vocabulary ending inside a
+    64-column group), against the same prompts probed 30 at a time.  Every maximum is tied four ways, between lane
+    halves (tokens 4 apart) and column halves (256 apart) of a tile: the lowest token wins."""
+    t = torch()
+    bf, k, P = t.bfloat16, 4, 5
+    top, layers = _world(t, B, d, 128, 1, 1, V)
+    ids = t.arange(V, device="cuda")
+    top["lm_head"] = top["lm_head"][ids & ~(4 | 256)].contiguous()
+    g = t.Generator(device="cuda").manual_seed(d)
+    pk, pv = t.randn(1, B, 1, P, 128, generator=g, device="cuda").to(bf), t.randn(1, B, 1, 1, 128, 64, generator=g, device="cuda").to(bf)
+    last = t.randn(B, V, generator=g, device="cuda")
+    m = rgd.Model(rgd.ModelConfig(1, d, 1, 1, 128, 128, V, rgd.DTYPE_BF16, 1e-5, 500000.0, 64), top, layers, B)
+
+    def probe(b0, b1):
+        n = b1 - b0
+        z = lambda *s: t.zeros(s, dtype=bf, device="cuda")  # noqa: E731
+        kv = rgd.KV(m, n, P, n, 16, pk[:, b0:b1], pv[:, b0:b1], z(1, n, 1, 16, 128), z(1, n, 1, 128, 16))
+        for b in range(n):
+            kv.set_prefix_len(b, P)
+        tok, length, event = (t.full(s, -5, dtype=t.int32, device="cuda") for s in ((n, k), (n,), (n,)))
+        rgd.probe(m, kv, last[b0:b1], None, n, k, 3, -1, tok, length, event)
+        return tok, length, event
+    got = probe(0, B)
+    lots = [probe(b, min(B, b + 30)) for b in range(0, B, 30)]
+    for x, parts in zip(got, zip(*lots)):
+        assert t.equal(x, t.cat(parts))
+    tok = got[0][:, 1:]
+    assert bool(((tok >= 0) & (tok < V) & (tok & (4 | 256) == 0)).all()) and bool((got[1] == k).all())
+    assert tok.unique().numel() > B  # prompts differ
+
+
 @pytest.mark.parametrize("heads,kv_heads", [(32, 8), (6, 2)])
 def test_tail_attention_of_many_rows(rgd, heads, kv_heads):
     """Rows of a batch large enough for one-wave tail workgroups against the same rows few at a time (four waves):
