@@ -64,7 +64,15 @@ constexpr float kNoRef = -3.0e38f;
 // split's output to bf16 before it), so both give the same bits.  Only a split with no
 // visible position (weight sum 0) is left out: a weight sum that is not a number,
 // from a NaN among the scores, enters like any other and makes the output NaN.
+// No products are fused into sums that are not written so: the walk has the
+// log-sum-exp of a split in registers, where lse - nm would become one fused operation with
+// the product that lse ends in, while the merge kernel reads it rounded from memory.
+RGD_DEV float split_lse(float m, float weights) {
+#pragma clang fp contract(off)
+  return weights != 0.f ? (m + __log2f(weights)) * kLn2 : -INFINITY;
+}
 RGD_DEV void merge_step(float& mx, float& den, float lse, float& a, float& b) {
+#pragma clang fp contract(off)
   const float nm = fmaxf(mx, lse);
   a = mx == -INFINITY ? 0.f : __expf(mx - nm);
   b = __expf(lse - nm);
@@ -406,7 +414,7 @@ __global__ __launch_bounds__(NW * 64) void attn_prefix_kernel(AttnArgs a, bf16_t
       const bool some = lt != 0.f;
       const float inv = some ? 1.0f / lt : 0.f;
       float wa = 1.f, wb = 0.f;
-      if (some) merge_step(wmx[nt], wden[nt], (m[nt] + __log2f(lt)) * kLn2, wa, wb);
+      if (some) merge_step(wmx[nt], wden[nt], split_lse(m[nt], lt), wa, wb);
 #pragma unroll
       for (int dt = 0; dt < (WALK ? 8 : 1); ++dt) {
 #pragma unroll
@@ -496,7 +504,7 @@ __global__ __launch_bounds__(NW * 64) void attn_prefix_kernel(AttnArgs a, bf16_t
       for (int dt = 0; dt < 8; ++dt)
         *(u32x2*)(po + dt * 16 + grp * 4) = u32x2{pack2(o[dt][nt][0] * inv, o[dt][nt][1] * inv),
                                                   pack2(o[dt][nt][2] * inv, o[dt][nt][3] * inv)};
-      if (grp == 0) a.part_lse[idx] = lt != 0.f ? (m[nt] + __log2f(lt)) * kLn2 : -INFINITY;
+      if (grp == 0) a.part_lse[idx] = split_lse(m[nt], lt);
     }
   }
 }

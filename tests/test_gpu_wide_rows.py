@@ -53,24 +53,25 @@ def _prefill(rgd, t, world, dims, tokens, max_rows):
 # in the chunks of 2100 (a 52-row last tile; 22 steps over 4 and 56 over 8; four and
 # eight heads per KV head), 2600 and, at d = 4096, 690 rows.  Rows of several
 # prompts in one chunk, with prefix splits of one and of three 64-position tiles.
-# The wide runs walk over the prefix splits in the attention, those of few rows
-# attend split by split, except in the first case (20 workgroups), the last
-# chunk of the second and the chunk of 5 x 30 tokens (10), which do not walk, and in the
-# chunk of 64 one-token prompts, which walks in both.  The last two cases: last rows that go
-# through the LM head prompt by prompt's chunk (held back, in two lots for 70
+# The attention walks over the prefix splits in the wide runs of 690, 2600 and 1300 rows and, with 32 query
+# heads, of 2100 (66 row blocks, two launches; two tiles per split) and 1300 (eight heads per KV head); all
+# other chunks, those of few rows among them, attend split by split.  The chunks of 150 and
+# 70 rows: last rows that go through the LM head prompt by prompt's chunk (held back, in two lots for 70
 # prompts) and in place.
 CASES = [((1024, 2816, 8, 4, 512), 1, 257, 300), ((1024, 5632, 8, 2, 512), 1, 700, 513),
          ((1024, 1408, 8, 2, 512), 1, 600, 600), ((1024, 3584, 8, 2, 512), 1, 2100, 2100),
          ((1024, 1408, 8, 1, 512), 1, 2100, 2100),
          ((4096, 1152, 32, 8, 512), 3, 230, 700), ((1024, 1408, 8, 8, 512), 2, 1300, 2600),
          ((1024, 1408, 8, 2, 512), 1, 1300, 1300), ((1024, 1408, 8, 2, 512), 1, 1000, 1000),
+         ((1024, 1408, 32, 8, 512), 1, 2100, 2100), ((1024, 128, 32, 4, 512), 1, 1300, 1300),
          ((1024, 128, 8, 2, 512), 5, 30, 150), ((1024, 128, 8, 2, 512), 70, 1, 70)]
 
 
 @pytest.mark.parametrize("dims,prompts,n,rows", CASES)
 def test_prefill_chunk_size_does_not_matter(rgd, dims, prompts, n, rows):
+    """Two layers: the second one's K/V show every row's attention and projections, the logits only the last row's."""
     t = torch()
-    world = _world(t, n, *dims)
+    world = _world(t, n, *dims, layers=2)
     g = t.Generator(device="cuda").manual_seed(n + 1)
     tokens = t.randint(0, dims[4], (prompts, n), generator=g, device="cuda", dtype=t.int32)
     few = _prefill(rgd, t, world, dims, tokens, 64)
