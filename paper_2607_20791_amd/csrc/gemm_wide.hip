@@ -16,9 +16,9 @@
 // on random inputs on gfx950, with either operand order), and the k order and
 // the splits are the same.
 //
-// Measured on one MI355X: 1.14-1.21 PFLOP/s at 2048 rows on random bf16 inputs
-// (SwiGLU and down projection of an 8B-class layer; 1.3-1.38 on zeros, so part
-// of the rest is power; a library product of 8192^3 reaches 1.36).  Eight waves of
+// Measured on one MI355X at 2048 rows of random bf16 inputs (8B-class layer): SwiGLU
+// 392-399 us, 1.21-1.23 PFLOP/s, down projection 201-216 us, 1.11-1.20 (1.3-1.38 on
+// zeros, so part of the rest is power; a library product of 8192^3 reaches 1.36).  Eight waves of
 // 64 x 64 (LDS traffic 176 instead of 144 KiB a step), 256-column tiles on two
 // LDS slots, a fourth weight slot and a wave that touches the weights ahead
 // were no faster.
