@@ -56,31 +56,22 @@ constexpr float kNoRef = -3.0e38f;
 #define RGD_ATTN_RING 5
 #endif
 
-// The partials of a row's prefix splits are combined one after the other, in
-// split order: with (mx, den) the running maximum of their log-sum-exps and the
-// sum of their weights relative to it, the outputs summed so far are scaled by a
-// and the next split's normalised output enters with weight b.  The kernel that
-// walks over all splits and the merge kernel share this step (and round a
-// split's output to bf16 before it), so both give the same bits.  Only a split with no
-// visible position (weight sum 0) is left out: a weight sum that is not a number,
-// from a NaN among the scores, enters like any other and makes the output NaN.
-// No products are fused into sums that are not written so: the walk has the
-// log-sum-exp of a split in registers, where lse - nm would become one fused operation with
-// the product that lse ends in, while the merge kernel reads it rounded from memory.
-RGD_DEV float split_lse(float m, float weights) {
-#pragma clang fp contract(off)
-  return weights != 0.f ? (m + __log2f(weights)) * kLn2 : -INFINITY;
-}
-RGD_DEV void merge_step(float& mx, float& den, float lse, float& a, float& b) {
-#pragma clang fp contract(off)
-  const float nm = fmaxf(mx, lse);
-  a = mx == -INFINITY ? 0.f : __expf(mx - nm);
-  b = __expf(lse - nm);
-  den = fmaf(den, a, b);
-  mx = nm;
-}
-RGD_DEV float merge_value(float o, float a, float b, float part) { return fmaf(b, part, o * a); }
-RGD_DEV float merge_lse(float mx, float den) { return den > 0.f ? mx + __logf(den) : -INFINITY; }
+// Log-sum-exp of one split of a query vector: m its exponent reference (log2 units),
+// `weights` the sum of its weights.  Only a split with no visible position (weight
+// sum 0) is left out of the merge: a weight sum that is not a number, from a NaN among
+// the scores, enters like any other and makes the output NaN.
+RGD_DEV float split_lse(float m, float weights) { return weights != 0.f ? (m + __log2f(weights)) * kLn2 : -INFINITY; }
+// The partials of a row's prefix splits are combined by these weights relative to the
+// largest log-sum-exp (over their sum), added in split order; the sum of the weights
+// is that of a butterfly over 64 lanes, lane k holding split k.  The kernel that walks
+// over all splits does the same in one lane per query vector, from log-sum-exps read
+// back from LDS, so both give the same bits.
+RGD_DEV float split_weight(float lse, float mx) { return lse == -INFINITY ? 0.f : __expf(lse - mx); }
+// A split's normalised output in bf16 (bounded by max|V|; the merged output is bf16 as
+// well), a row of D values: dims 16 dt + 4 grp + {0..3} of a prefix kernel lane sit at
+// (dt / 2) * 32 + grp * 8 + (dt % 2) * 4, so that a lane stores 16 bytes at a time
+// and the four lanes of a query vector 64 side by side.
+RGD_DEV int part_slot(int dim) { return (dim >> 5) * 32 + ((dim >> 2) & 3) * 8 + ((dim >> 4) & 1) * 4 + (dim & 3); }
 
 // K tiles sit in LDS as unpadded 256-byte rows whose 16-byte chunks are
 // XOR-swizzled: chunk c of row r is stored at chunk c ^ kswz(r).  A fragment
@@ -116,14 +107,19 @@ RGD_DEV int k_gather_row(int h, int e, int l16) { return h * 32 + (l16 >> 2) * 8
 // the scores of tile t+1 are computed (MFMA) while the softmax of tile t runs
 // on the vector units.  One barrier per tile.
 //
-// WALK: one workgroup per (KV head, row block) walks over all splits, closes
-// each at its end as a separate workgroup would and merges it into a second set of
-// accumulators.  Rows whose prefix ends with the walk are written out, those with
-// positions left for the tail kernel leave their merged partial (fp32) and its
-// log-sum-exp as partial 0.  2048 rows, 32 heads, 4096 positions, first / second
-// half: 67 / 205 us, against 155 / 310 split and 115 / 140 for the merge of the
-// partials (four waves of twice the query vectors 90 / 250: one wave per SIMD
-// hides too little).
+// WALK: one workgroup per (KV head, row block) walks over all splits and closes each
+// at its end as a separate workgroup would.  Rows whose prefix ends with the walk are
+// merged at its end by the lanes that hold them, the first split's partial from
+// LDS, those of the next kWalkRegs and the last one from registers, the rest read back
+// from memory; rows with positions left get all their partials written and are merged
+// by the tail kernel.
+constexpr int kMaxWalkSplits = 40;
+// (registers of two waves per SIMD, which the LDS allows: 256)
+#ifndef RGD_WALK_REGS
+#define RGD_WALK_REGS 5
+#endif
+constexpr int kWalkRegs = RGD_WALK_REGS;
+
 template <int NW, int NQ, bool WALK>
 __global__ __launch_bounds__(NW * 64) void attn_prefix_kernel(AttnArgs a, bf16_t* out) {
   constexpr int D = 128, TP = 64, NT = NW * 64, NB = 3;
@@ -133,7 +129,7 @@ __global__ __launch_bounds__(NW * 64) void attn_prefix_kernel(AttnArgs a, bf16_t
   const int4 rb = a.rblk[WALK ? gridDim.z - 1 - blockIdx.z : blockIdx.z];
   const int r0 = rb.x, nr = rb.y, b = rb.z, maxplen = rb.w;
   const int lo = s * a.split_len;
-  const int hi = WALK ? maxplen : min(lo + a.split_len, maxplen);
+  const int hi = WALK ? prefix_part_end(maxplen, a.split_len) : min(lo + a.split_len, maxplen);
   const int G = a.Hq / a.Hkv;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int l16 = lane & 15, grp = lane >> 4;
@@ -193,16 +189,13 @@ __global__ __launch_bounds__(NW * 64) void attn_prefix_kernel(AttnArgs a, bf16_t
 #pragma unroll
     for (int dt = 0; dt < 8; ++dt) o[dt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-  // WALK: the splits merged so far
-  float wmx[NQ], wden[NQ];
-  f32x4 wo[WALK ? 8 : 1][NQ];
+  // WALK: log-sum-exps of the closed splits, their largest, and the first split's partials
+  __shared__ float walk_lse[WALK ? kMaxWalkSplits : 1][WALK ? RGD_ATTN_QV : 1];
+  __shared__ u32x4 walk_p0[WALK ? NQ * 4 * NT : 1];
+  u32x4 walk_p[WALK ? kWalkRegs : 1][NQ][4];  // partials of the next kWalkRegs splits
+  float wmx[NQ];
 #pragma unroll
-  for (int nt = 0; nt < NQ; ++nt) {
-    wmx[nt] = -INFINITY;
-    wden[nt] = 0.f;
-#pragma unroll
-    for (int dt = 0; dt < (WALK ? 8 : 1); ++dt) wo[dt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  }
+  for (int nt = 0; nt < NQ; ++nt) wmx[nt] = -INFINITY;
   const u32x4 ones = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};  // bf16 1.0 x 8
 
   // Register staging of the next tile.  Nothing reads these registers before
@@ -406,30 +399,51 @@ __global__ __launch_bounds__(NW * 64) void attn_prefix_kernel(AttnArgs a, bf16_t
     }
   };
 
-  // WALK: ends the split of the tile just done
-  auto close_split = [&]() __attribute__((always_inline)) {
+  // the partial of the split just done: word pair dt % 2 of p[dt / 2]
+  auto pack_split = [&](int nt, u32x4 (&p)[4]) __attribute__((always_inline)) {
+    const float lt = lacc[nt][0], inv = lt > 0.f ? 1.0f / lt : 0.f;
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt) {
+      p[dt >> 1][(dt & 1) * 2] = pack2(o[dt][nt][0] * inv, o[dt][nt][1] * inv);
+      p[dt >> 1][(dt & 1) * 2 + 1] = pack2(o[dt][nt][2] * inv, o[dt][nt][3] * inv);
+    }
+  };
+  auto part_at = [&](int sp, int nt) {
+    return (bf16_t*)a.part_o + (((long long)sp * a.rows.R + vrow[nt]) * a.Hq + vhead[nt]) * D + grp * 8;
+  };
+  auto write_part = [&](int sp, int nt, const u32x4 (&p)[4]) __attribute__((always_inline)) {
+    bf16_t* po = part_at(sp, nt);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) *(u32x4*)(po + j * 32) = p[j];
+    if (grp == 0) a.part_lse[((long long)sp * a.rows.R + vrow[nt]) * a.Hq + vhead[nt]] = split_lse(m[nt], lacc[nt][0]);
+  };
+  auto ends_here = [&](int nt) { return prefix_part_end(pl[nt], a.split_len) == pl[nt]; };
+  auto lse_slot = [&](int nt) { return WALK ? (wave * NQ + nt) * 16 + l16 : 0; };
+  auto p0_slot = [&](int nt, int j) { return WALK ? ((wave * NQ + nt) * 4 + j) * 64 + lane : 0; };
+  // WALK: ends split sp, which is not the last
+  auto close_split = [&](int sp) __attribute__((always_inline)) {
 #pragma unroll
     for (int nt = 0; nt < NQ; ++nt) {
-      const float lt = lacc[nt][0];
-      const bool some = lt != 0.f;
-      const float inv = some ? 1.0f / lt : 0.f;
-      float wa = 1.f, wb = 0.f;
-      if (some) merge_step(wmx[nt], wden[nt], split_lse(m[nt], lt), wa, wb);
+      const float lse = split_lse(m[nt], lacc[nt][0]);
+      u32x4 p[4];
+      pack_split(nt, p);
+      if (sp == 0) {
 #pragma unroll
-      for (int dt = 0; dt < (WALK ? 8 : 1); ++dt) {
-#pragma unroll
-        for (int w = 0; w < 2; ++w) {
-          const uint32_t p = pack2(o[dt][nt][2 * w] * inv, o[dt][nt][2 * w + 1] * inv);
-          const float p0 = __uint_as_float(p << 16), p1 = __uint_as_float(p & 0xFFFF0000u);
-          if (some) {
-            wo[dt][nt][2 * w] = merge_value(wo[dt][nt][2 * w], wa, wb, p0);
-            wo[dt][nt][2 * w + 1] = merge_value(wo[dt][nt][2 * w + 1], wa, wb, p1);
-          }
-        }
-        o[dt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < 4; ++j) walk_p0[p0_slot(nt, j)] = p[j];
       }
+#pragma unroll
+      for (int i = 0; i < (WALK ? kWalkRegs : 0); ++i)
+        if (sp == 1 + i) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) walk_p[i][nt][j] = p[j];
+        }
+      if (vok[nt] && (sp > kWalkRegs || !ends_here(nt))) write_part(sp, nt, p);
+      if (grp == 0) walk_lse[WALK ? sp : 0][lse_slot(nt)] = lse;
+      wmx[nt] = fmaxf(wmx[nt], lse);
       m[nt] = kNoRef;
       lacc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int dt = 0; dt < 8; ++dt) o[dt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
   };
   const int ntile = hi > lo ? (hi - lo + TP - 1) / TP : 0;
@@ -463,7 +477,7 @@ __global__ __launch_bounds__(NW * 64) void attn_prefix_kernel(AttnArgs a, bf16_t
         prime(nb, 0, cb, 1, ring);
         prepare(t0 + 32, sb);
         stream(nb, 0, cb, 1, sb, sa, ring);
-        if (WALK && ((t + 1) % tiles_split == 0 || t + 1 == ntile)) close_split();  // uniform
+        if (WALK && (t + 1) % tiles_split == 0 && t + 1 < ntile) close_split(t / tiles_split);  // uniform
       }
     };
     static_assert(NB == 3, "the tile loop is unrolled by the number of LDS tile buffers");
@@ -474,37 +488,85 @@ __global__ __launch_bounds__(NW * 64) void attn_prefix_kernel(AttnArgs a, bf16_t
     }
   }
 
-  if (WALK) {
+  if constexpr (!WALK) {
+#pragma unroll
+    for (int nt = 0; nt < NQ; ++nt) {
+      u32x4 p[4];
+      pack_split(nt, p);
+      if (vok[nt]) write_part(s, nt, p);
+    }
+  } else {
+    const int ns = (ntile + tiles_split - 1) / tiles_split;
+#pragma unroll
+    for (int nt = 0; nt < NQ; ++nt)
+      if (grp == 0) walk_lse[ns - 1][lse_slot(nt)] = split_lse(m[nt], lacc[nt][0]);
+    __syncthreads();
 #pragma unroll
     for (int nt = 0; nt < NQ; ++nt) {
       if (!vok[nt]) continue;
-      const long long idx = (long long)vrow[nt] * a.Hq + vhead[nt];
-      const float inv = wden[nt] > 0.f ? 1.0f / wden[nt] : 0.f;
-      const bool done = prefix_part_end(pl[nt], a.split_len) == pl[nt];
-#pragma unroll
-      for (int dt = 0; dt < (WALK ? 8 : 1); ++dt) {
-        const f32x4 y = wo[dt][nt] * inv;
-        if (done) *(u32x2*)(out + idx * D + dt * 16 + grp * 4) = u32x2{pack2(y[0], y[1]), pack2(y[2], y[3])};
-        else *(f32x4*)(a.part_o + idx * D + dt * 16 + grp * 4) = y;
+      u32x4 pn[4];
+      pack_split(nt, pn);
+      if (!ends_here(nt)) {
+        write_part(ns - 1, nt, pn);
+        continue;
       }
-      if (!done && grp == 0) a.part_lse[idx] = merge_lse(wmx[nt], wden[nt]);
-    }
-    return;
-  }
+      // (log-sum-exps come back from LDS: in registers, lse - max would be fused with the
+      // product that lse ends in, unrounded)
+      const float* lses = &walk_lse[0][lse_slot(nt)];
+      const float mx = fmaxf(wmx[nt], lses[(ns - 1) * RGD_ATTN_QV]);
+      auto weight = [&](int k) { return k < ns ? split_weight(lses[min(k, ns - 1) * RGD_ATTN_QV], mx) : 0.f; };
+      // the sum over 64 lanes halved 32, 16, 8, 4, 2, 1 apart (kMaxWalkSplits <= 48)
+      float d[16];
 #pragma unroll
-  for (int nt = 0; nt < NQ; ++nt) {
-    const float lt = lacc[nt][0];
-    if (vok[nt]) {
-      const long long idx = ((long long)s * a.rows.R + vrow[nt]) * a.Hq + vhead[nt];
-      // normalised partial output, stored in bf16 (bounded by max|V|; the
-      // merged output is bf16 as well)
-      bf16_t* po = (bf16_t*)a.part_o + idx * D;
-      const float inv = lt > 0.f ? 1.0f / lt : 0.f;
+      for (int k = 0; k < 16; ++k) {
+        d[k] = weight(k);
+        if (ns > 32) d[k] += weight(k + 32);
+        if (ns > 16) d[k] += weight(k + 16);
+      }
 #pragma unroll
-      for (int dt = 0; dt < 8; ++dt)
-        *(u32x2*)(po + dt * 16 + grp * 4) = u32x2{pack2(o[dt][nt][0] * inv, o[dt][nt][1] * inv),
-                                                  pack2(o[dt][nt][2] * inv, o[dt][nt][3] * inv)};
-      if (grp == 0) a.part_lse[idx] = split_lse(m[nt], lt);
+      for (int h = 8; h > 0; h >>= 1)
+#pragma unroll
+        for (int k = 0; k < h; ++k) d[k] += d[k + h];
+      const float inv = d[0] > 0.f ? 1.f / d[0] : 0.f;
+      f32x4 y[8];
+#pragma unroll
+      for (int dt = 0; dt < 8; ++dt) y[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+      auto add = [&](int k, const u32x4 (&p)[4]) __attribute__((always_inline)) {
+        const float lse = lses[k * RGD_ATTN_QV], wk = split_weight(lse, mx) * inv;
+        if (lse == -INFINITY) return;
+#pragma unroll
+        for (int dt = 0; dt < 8; ++dt)
+#pragma unroll
+          for (int w = 0; w < 2; ++w) {
+            const uint32_t x = p[dt >> 1][(dt & 1) * 2 + w];
+            y[dt][2 * w] = fmaf(wk, __uint_as_float(x << 16), y[dt][2 * w]);
+            y[dt][2 * w + 1] = fmaf(wk, __uint_as_float(x & 0xFFFF0000u), y[dt][2 * w + 1]);
+          }
+      };
+      if (ns > 1) {
+        u32x4 p[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) p[j] = walk_p0[p0_slot(nt, j)];
+        add(0, p);
+      }
+#pragma unroll
+      for (int i = 0; i < kWalkRegs; ++i)
+        if (1 + i < ns - 1) add(1 + i, walk_p[i][nt]);
+      // four splits' loads at a time
+      for (int k0 = 1 + kWalkRegs; k0 < ns - 1; k0 += 4) {
+        u32x4 p[4][4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) p[u][j] = *(const u32x4*)(part_at(min(k0 + u, ns - 2), nt) + j * 32);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (k0 + u < ns - 1) add(k0 + u, p[u]);
+      }
+      add(ns - 1, pn);
+      bf16_t* y0 = out + ((long long)vrow[nt] * a.Hq + vhead[nt]) * D + grp * 4;
+#pragma unroll
+      for (int dt = 0; dt < 8; ++dt) *(u32x2*)(y0 + dt * 16) = u32x2{pack2(y[dt][0], y[dt][1]), pack2(y[dt][2], y[dt][3])};
     }
   }
 }
@@ -763,9 +825,10 @@ __global__ __launch_bounds__(256) void attn_tail_combine_kernel(AttnArgs a, floa
 // (K rows in the gathered order of the prefix kernel, so every lane ends up with
 // eight consecutive positions).  The four states are merged through LDS in a fixed
 // order, and a head's output is written by one wave.  The merge is in log-sum-exp
-// form: a head's prefix-split partials are combined in split order (for the wave's
-// first head while its first tile is loading), which leaves a two-term merge with
-// the tail after the exchange.
+// form.  The prefix-split partials of heads 0 .. 3 are combined into one first (of
+// the wave's first head while its first tile is loading), which leaves a two-term merge
+// with the tail after the exchange; the partials of further heads (G > 4) and their
+// tail are merged in one go.
 // NWV: waves per workgroup.  Four take one lane of work each: the shortest chain,
 // for few (row, head) pairs.  One takes all four in turn: a workgroup's start and
 // merge cost more than a tile, and with enough pairs to fill the chip fewer, longer
@@ -774,14 +837,14 @@ __global__ __launch_bounds__(256) void attn_tail_combine_kernel(AttnArgs a, floa
 // 64 59.8 / 55.6, 200 84.4 / 81.9.  The states and their merge are the same, so the
 // bits are too.
 // GM: query heads per KV head at most (LDS).
-// WALKED: the splits come combined, as one fp32 partial, and the rows are those of
-// a list.
+// LIST: the rows are those of a list, left by a walk, which writes the partials of
+// the splits that a row's prefix reaches.
 constexpr int kMergeMaxSplits = 64;
 
-template <bool WALKED, int NWV, int GM>
+template <bool LIST, int NWV, int GM>
 __global__ __launch_bounds__(NWV * 64) void attn_tail_merge_kernel(AttnArgs a, bf16_t* out, const int* rowlist) {
   constexpr int D = 128, TT = 32;
-  const int r = WALKED ? rowlist[blockIdx.x] : blockIdx.x, g = blockIdx.y;
+  const int r = LIST ? rowlist[blockIdx.x] : blockIdx.x, g = blockIdx.y;
   const int G = a.Hq / a.Hkv;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int l16 = lane & 15, grp = lane >> 4;
@@ -810,28 +873,20 @@ __global__ __launch_bounds__(NWV * 64) void attn_tail_merge_kernel(AttnArgs a, b
   // request those of this wave's first head now so their latency overlaps the
   // tail attention (splits beyond kPrefetch are loaded by the combine).
   const int S = a.splits;
-  constexpr int kPrefetch = 16;
+  constexpr int kPrefetch = NWV == 1 ? 1 : 16;
   const long long pstep = R * a.Hq * D;
   // (Loads in this kernel are unconditional, from clamped addresses, and
   // masked afterwards: a predicated load makes the compiler wait for it where
   // the branches join, one memory round trip each.)
   // (a wave past the G heads loads head G-1's and does not use them)
-  uint32_t pre[WALKED ? 2 : kPrefetch];  // bf16 pairs (WALKED: the two fp32 values)
+  uint32_t pre[kPrefetch];  // bf16 pairs
   float pre_lse;
   {
     const int head = g * G + min(wave, G - 1);
-    const long long i0 = ((long long)r * a.Hq + head) * D + 2 * lane;
-    if constexpr (WALKED) {
-      const u32x2 v = *(const u32x2*)(a.part_o + i0);
-      pre[0] = v[0];
-      pre[1] = v[1];
-      pre_lse = a.part_lse[(long long)r * a.Hq + head];
-    } else {
-      const bf16_t* po = (const bf16_t*)a.part_o + i0;
+    const bf16_t* po = (const bf16_t*)a.part_o + ((long long)r * a.Hq + head) * D + part_slot(2 * lane);
 #pragma unroll
-      for (int k = 0; k < kPrefetch; ++k) pre[k] = *(const uint32_t*)(po + min(k, S - 1) * pstep);
-      pre_lse = a.part_lse[((long long)min(lane, S - 1) * R + r) * a.Hq + head];
-    }
+    for (int k = 0; k < kPrefetch; ++k) pre[k] = *(const uint32_t*)(po + min(k, S - 1) * pstep);
+    pre_lse = a.part_lse[((long long)min(lane, S - 1) * R + r) * a.Hq + head];
   }
 
   u32x4 qf[4];
@@ -844,51 +899,62 @@ __global__ __launch_bounds__(NWV * 64) void attn_tail_merge_kernel(AttnArgs a, b
       qf[ks] = ok ? x : u32x4{0u, 0u, 0u, 0u};
     }
   }
+  const int pe = prefix_part_end(plen, a.split_len);
+  const int nsp = LIST ? (pe + a.split_len - 1) / a.split_len : S;  // splits with a partial
+  // o += the split partials of a head by their weights (lane k holds split k's), in
+  // split order; a split without positions is left out
+  auto add_splits = [&](const bf16_t* po, float lses, float w, float inv, bool first, float& o0, float& o1) {
+    auto add = [&](int k, uint32_t v) {
+      if (__int_as_float(__builtin_amdgcn_readlane(__float_as_int(lses), k)) == -INFINITY) return;  // uniform
+      const float wk = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), k)) * inv;
+      o0 = fmaf(wk, __uint_as_float(v << 16), o0);
+      o1 = fmaf(wk, __uint_as_float(v & 0xFFFF0000u), o1);
+    };
+    if (first) {
+#pragma unroll
+      for (int k = 0; k < kPrefetch; ++k)
+        if (k < nsp) add(k, pre[k]);
+    }
+    // eight splits' loads at a time
+    for (int k0 = first ? kPrefetch : 0; k0 < nsp; k0 += 8) {
+      uint32_t v[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) v[k] = *(const uint32_t*)(po + min(k0 + k, S - 1) * pstep);
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        if (k0 + k < nsp) add(k0 + k, v[k]);
+    }
+  };
+  auto butterfly = [&](float v) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    return v;
+  };
   // The prefix splits of one head combined into one partial (log-sum-exp
   // s_lse, normalised output s_o0 / s_o1 for dims 2*lane, 2*lane+1).  It needs no
   // tail data: the first head's is formed while the first tile's loads are in
   // flight.  Lane sp holds split sp's log-sum-exp.
   float s_lse = -INFINITY, s_o0 = 0.f, s_o1 = 0.f;
   auto combine_splits = [&](int head, float lses, bool first) {
-    if constexpr (WALKED) {
+    if (NWV == 1 || S == 1) {  // its weight is 1 (every lane holds its log-sum-exp)
+      const uint32_t v = first ? pre[0] : *(const uint32_t*)((const bf16_t*)a.part_o + ((long long)r * a.Hq + head) * D + part_slot(2 * lane));
       s_lse = lses;
-      s_o0 = __uint_as_float(pre[0]);
-      s_o1 = __uint_as_float(pre[1]);
-      if (!first) {
-        const float* po = a.part_o + ((long long)r * a.Hq + head) * D + 2 * lane;
-        s_o0 = po[0];
-        s_o1 = po[1];
-      }
-    } else {
-      float mx = -INFINITY, den = 0.f, o0 = 0.f, o1 = 0.f;
-      auto add = [&](int k, uint32_t v) {
-        const float l = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lses), k));
-        if (l == -INFINITY) return;  // uniform: no position of this split
-        float wa, wb;
-        merge_step(mx, den, l, wa, wb);
-        o0 = merge_value(o0, wa, wb, __uint_as_float(v << 16));
-        o1 = merge_value(o1, wa, wb, __uint_as_float(v & 0xFFFF0000u));
-      };
-      const bf16_t* po = (const bf16_t*)a.part_o + ((long long)r * a.Hq + head) * D + 2 * lane;
-      if (first) {
-#pragma unroll
-        for (int k = 0; k < kPrefetch; ++k)
-          if (k < S) add(k, pre[k]);
-      }
-#pragma unroll 1
-      for (int k = first ? kPrefetch : 0; k < S; ++k) add(k, *(const uint32_t*)(po + k * pstep));
-      const float inv = den > 0.f ? 1.f / den : 0.f;
-      s_lse = merge_lse(mx, den);
-      s_o0 = o0 * inv;
-      s_o1 = o1 * inv;
+      s_o0 = __uint_as_float(v << 16);
+      s_o1 = __uint_as_float(v & 0xFFFF0000u);
+      return;
     }
+    lses = lane < nsp ? lses : -INFINITY;
+    const float mx = wave_max(lses), w = split_weight(lses, mx), den = butterfly(w);
+    const float inv = den > 0.f ? 1.f / den : 0.f;
+    s_lse = den > 0.f ? mx + __logf(den) : -INFINITY;
+    s_o0 = s_o1 = 0.f;
+    add_splits((const bf16_t*)a.part_o + ((long long)r * a.Hq + head) * D + part_slot(2 * lane), lses, w, inv, first, s_o0, s_o1);
   };
   bool combined = false;
   // the row's own positions: first its prefix positions the split kernel left
   // (fewer than 64 past a split boundary, read in place from the shared
   // prefix), then its paged tail; 32-position tiles of either, dealt to the
   // four waves in turn
-  const int pe = prefix_part_end(plen, a.split_len);
   const int n_ovt = (plen - pe + TT - 1) / TT, n_all = n_ovt + (n + TT - 1) / TT;
   const long long bg = (long long)prompt * a.Hkv + g;
   const bf16_t* pk = (const bf16_t*)a.kv.prefix_k + bg * a.kv.P * D;
@@ -1002,7 +1068,7 @@ __global__ __launch_bounds__(NWV * 64) void attn_tail_merge_kernel(AttnArgs a, b
   __syncthreads();
 
   // merge: wave h handles query heads h, h + NWV, ...; lane holds dims 2*lane, 2*lane+1
-  auto finish = [&](int h) {
+  auto finish = [&](int h, float lses) {
     const int head = g * G + h;
     // tail state of this head (exp2 domain) from the four waves
     float tm = -INFINITY;
@@ -1019,22 +1085,34 @@ __global__ __launch_bounds__(NWV * 64) void attn_tail_merge_kernel(AttnArgs a, b
       }
     }
     const float tail_lse = tl > 0.f ? (tm + __log2f(tl)) * kLn2 : -INFINITY;
-    // the prefix splits are combined already: two partials left
-    const float mx = fmaxf(s_lse, tail_lse);
-    const float ws = s_lse == -INFINITY ? 0.f : __expf(s_lse - mx);
-    const float wt = tail_lse == -INFINITY ? 0.f : __expf(tail_lse - mx);
-    const float den = ws + wt;
+    if (NWV == 1 || h < 4) {  // the prefix splits are combined already: two partials left
+      const float mx = fmaxf(s_lse, tail_lse);
+      const float ws = s_lse == -INFINITY ? 0.f : __expf(s_lse - mx);
+      const float wt = tail_lse == -INFINITY ? 0.f : __expf(tail_lse - mx);
+      const float den = ws + wt;
+      const float inv = den > 0.f ? 1.f / den : 0.f;
+      const float ft = tl > 0.f ? wt * inv / tl : 0.f;  // applied to the unnormalised tail sum
+      const float fs = ws * inv;
+      *(uint32_t*)(out + ((long long)r * a.Hq + head) * D + 2 * lane) =
+          pack_bf16x2(fs * s_o0 + ft * to0, fs * s_o1 + ft * to1);
+      return;
+    }
+    const float ls = lane < nsp ? lses : -INFINITY;
+    const float mx = wave_max(fmaxf(ls, tail_lse));
+    const float w = split_weight(ls, mx), wt = split_weight(tail_lse, mx);
+    const float den = butterfly(w) + wt;
     const float inv = den > 0.f ? 1.f / den : 0.f;
     const float ft = tl > 0.f ? wt * inv / tl : 0.f;  // applied to the unnormalised tail sum
-    const float fs = ws * inv;
-    *(uint32_t*)(out + ((long long)r * a.Hq + head) * D + 2 * lane) =
-        pack_bf16x2(fs * s_o0 + ft * to0, fs * s_o1 + ft * to1);
+    float o0 = ft * to0, o1 = ft * to1;
+    add_splits((const bf16_t*)a.part_o + ((long long)r * a.Hq + head) * D + part_slot(2 * lane), ls, w, inv, false, o0, o1);
+    *(uint32_t*)(out + ((long long)r * a.Hq + head) * D + 2 * lane) = pack_bf16x2(o0, o1);
   };
-  if (wave < G) finish(wave);
+  if (wave < G) finish(wave, 0.f);
   for (int h = wave + NWV; h < G; h += NWV) {  // further heads
     const int head = g * G + h;
-    combine_splits(head, a.part_lse[((long long)(WALKED ? 0 : min(lane, S - 1)) * R + r) * a.Hq + head], false);
-    finish(h);
+    const float lses = a.part_lse[((long long)min(lane, S - 1) * R + r) * a.Hq + head];
+    if (NWV == 1 || h < 4) combine_splits(head, lses, false);
+    finish(h, lses);
   }
 }
 
@@ -1042,6 +1120,7 @@ __global__ __launch_bounds__(NWV * 64) void attn_tail_merge_kernel(AttnArgs a, b
 
 hipError_t attn_prefix_bf16(const AttnArgs& a, bf16_t* out, hipStream_t s) {
   if (a.D != 128 || a.Hq / a.Hkv > RGD_ATTN_QV || a.split_len % 64 || a.kv.VP % 64) return hipErrorInvalidValue;
+  if (a.walk && a.splits > kMaxWalkSplits) return hipErrorInvalidValue;
   if (a.splits <= 0 || a.nrblocks <= 0) return hipSuccess;
   if (!a.rblocks) return hipErrorInvalidValue;
   // one launch per kAttnInlineBlocks row blocks
@@ -1102,7 +1181,7 @@ hipError_t attn_tail_merge_bf16(const AttnArgs& a, bf16_t* out, hipStream_t s) {
   // to merge per head (with 16 splits of an 8193-position prompt the serial loads of
   // four heads' partials cost more: 117 against 111 us)
   const int G = a.Hq / a.Hkv;
-  const bool one = G <= 4 && (a.walk || a.splits == 1) && (long long)rows * a.Hkv >= 2048;
+  const bool one = G <= 4 && a.splits == 1 && (long long)rows * a.Hkv >= 2048;
   const dim3 grid(rows, a.Hkv);
   if (a.walk) {
     if (one) hipLaunchKernelGGL((attn_tail_merge_kernel<true, 1, 4>), grid, dim3(64), 0, s, a, out, a.left);

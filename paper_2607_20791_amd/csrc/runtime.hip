@@ -331,38 +331,38 @@ struct RowArrays {
 
 // Whether a prefill chunk's attention walks over the prefix splits, one workgroup
 // per (row block, KV head), instead of one workgroup per split whose partials
-// the tail kernel merges for every row.  A walk writes no partials (a 2048-row
-// chunk at 4096 positions: 210 MB) and most rows need no tail kernel, but it
-// runs its tiles one after the other on few CUs.  Costs in units of 0.01 us, fitted
-// to 350 measured chunks (1 to 8 KV heads, 1 to 8 query heads each, 64-2048 rows, up
-// to 8192 positions; the side taken is 0.1% slower than the better one on average, 6%
-// at worst): 100 per 64-position tile and round of 256 workgroups, 200 per round of
-// split workgroups and per split that a walk closes, then the tail kernel with
-// the partials that its four waves load per row and KV head, and its workgroups.
+// the tail kernel merges for every row.  A walk keeps the partials of seven splits in
+// registers and LDS and most rows need no tail kernel, but it runs its tiles one after
+// the other on few CUs.  Costs in units of 0.01 us, fitted to 450 measured chunks (1
+// to 8 KV heads, 1 to 8 query heads each, 64-2048 rows, one to eight prompts, up to 8048
+// positions; the side taken is 0.3% slower than the better one on average, 14% at worst):
+// a walk's launch, 130 per 64-position tile and 148 per split in each round of 256
+// workgroups, then the tail kernel for the rows left; a launch of split workgroups, 88
+// per tile and round, then the tail kernel for all rows and their partials.
 // Attention stage, us, split / walk, one prompt, 32 query and 8 KV heads: 256 rows
-// at 1024 positions 57 / 66, 512 rows 101 / 71 and at 8192 positions 155 / 185, 1024
-// rows at 8192 303 / 212; 8 and 2 heads: 512 rows at 1024 35 / 58, 2048 at 4096 175 / 137.
+// after 1000 positions 50 / 67, 512 86 / 91, 1024 184 / 137 and after 6000 267 / 201,
+// 2048 rows after 3000 456 / 269; 8 and 2 heads: 2048 rows after 3000 177 / 221.
 void plan_walk(const rgd_model* m, const rgd_kv* kv, HostRows& h) {
   h.walk = false;
   h.left.clear();
   if (!m->bf16) return;
   const int len = kv->layer(0).split_len;
+  for (size_t r = 0; r < h.plen.size(); ++r)
+    if (prefix_part_end(h.plen[r], len) != h.plen[r]) h.left.push_back((int)r);
   const long long R = (long long)h.plen.size(), Hkv = m->cfg.n_kv_heads, Hq = m->cfg.n_heads;
-  const long long S = cdiv(h.maxplen, len);
-  long long walk = 270 + 120 * R * Hkv / 1000;
-  long long split = (6 * std::max(4 * Hkv, Hq) + 15 * Hq) * R * S / 1000 + 400 * R * Hkv / 1000;
+  const long long S = cdiv(h.maxplen, len), left = (long long)h.left.size();
+  long long walk = left * Hkv + left * Hq * S / 200;
+  long long split = 7 * R * Hkv / 10 + 18 * R * S * Hq / 1000;
   for (size_t b0 = 0; b0 < h.blocks.size(); b0 += kAttnInlineBlocks) {  // one launch of the kernel
     const size_t nb = std::min<size_t>(kAttnInlineBlocks, h.blocks.size() - b0);
     int longest = 0;
     for (size_t i = 0; i < nb; ++i) longest = std::max(longest, h.blocks[b0 + i].w);
     const long long tiles = cdiv(longest, 64), ns = cdiv(longest, len);
-    walk += cdiv((long long)nb * Hkv, 256) * (100 * tiles + 200 * ns);
-    split += cdiv((long long)nb * Hkv * ns, 256) * (100 * std::min<long long>(len / 64, tiles) + 200);
+    walk += 1460 + cdiv((long long)nb * Hkv, 256) * (130 * tiles + 148 * ns);
+    split += 1620 + cdiv((long long)nb * Hkv * ns, 256) * 88 * std::min<long long>(len / 64, tiles);
   }
-  if (walk >= split) return;
-  h.walk = true;
-  for (size_t r = 0; r < h.plen.size(); ++r)
-    if (prefix_part_end(h.plen[r], len) != h.plen[r]) h.left.push_back((int)r);
+  h.walk = walk < split;
+  if (!h.walk) h.left.clear();
 }
 
 // pages null: a call without tails

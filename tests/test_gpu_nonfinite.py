@@ -62,8 +62,8 @@ def test_prefill_over_a_resident_prefix(rgd, max_rows):
     """Chunks attended split by split and (1000 rows) in a walk over the splits."""
     t = torch()
     n0, n, V = 100, 1000, 256
-    top, layers = _world(t, 8, 8, V)
-    m = rgd.Model(rgd.ModelConfig(1, 128, 8, 8, D, 128, V, rgd.DTYPE_BF16, 1e-5, 500000.0, n0 + n), top, layers, max_rows)
+    top, layers = _world(t, 32, 8, V)
+    m = rgd.Model(rgd.ModelConfig(1, 128, 32, 8, D, 128, V, rgd.DTYPE_BF16, 1e-5, 500000.0, n0 + n), top, layers, max_rows)
     z = lambda *s: t.zeros(s, dtype=t.bfloat16, device="cuda")  # noqa: E731
     pk = z(1, 1, 8, n0 + n, D)
     kv = rgd.KV(m, 1, n0 + n, 0, 16, pk, z(1, 1, 8, (n0 + n + 63) // 64, D, 64), z(1, 1, 8, 16, D), z(1, 1, 8, D, 16))
