@@ -67,6 +67,7 @@ RGD_DEV float split_lse(float m, float weights) { return weights != 0.f ? (m + _
 // over all splits does the same in one lane per query vector, from log-sum-exps read
 // back from LDS, so both give the same bits.
 RGD_DEV float split_weight(float lse, float mx) { return lse == -INFINITY ? 0.f : __expf(lse - mx); }
+RGD_DEV float merged_lse(float mx, float den) { return den > 0.f ? mx + __logf(den) : -INFINITY; }
 // A split's normalised output in bf16 (bounded by max|V|; the merged output is bf16 as
 // well), a row of D values: dims 16 dt + 4 grp + {0..3} of a prefix kernel lane sit at
 // (dt / 2) * 32 + grp * 8 + (dt % 2) * 4, so that a lane stores 16 bytes at a time
@@ -107,14 +108,18 @@ RGD_DEV int k_gather_row(int h, int e, int l16) { return h * 32 + (l16 >> 2) * 8
 // the scores of tile t+1 are computed (MFMA) while the softmax of tile t runs
 // on the vector units.  One barrier per tile.
 //
-// WALK: one workgroup per (KV head, row block) walks over all splits and closes each
-// at its end as a separate workgroup would.  Rows whose prefix ends with the walk are
-// merged at its end by the lanes that hold them, the first split's partial from
-// LDS, those of the next kWalkRegs and the last one from registers, the rest read back
-// from memory; rows with positions left get all their partials written and are merged
-// by the tail kernel.
+// WALK: one workgroup per (KV head, row block) walks over all splits, closes each
+// at its end as a separate workgroup would and merges them at the end, in the lanes
+// that hold them: the first split's partial from LDS, those of the next kWalkRegs and
+// the last one from registers, the rest read back from memory.  Rows whose prefix ends with
+// the walk are written out, those with positions left for the tail kernel leave their
+// merged partial (fp32) and its log-sum-exp as partial 0.  With more than four heads per
+// KV head the tail kernel merges those rows itself, from all their partials.  2048 rows,
+// 32 heads, 4096 positions, first / second half: 84 / 225 us, against 155 / 310 split
+// and 115 / 140 for the merge of the partials.
 constexpr int kMaxWalkSplits = 40;
-// (registers of two waves per SIMD, which the LDS allows: 256)
+// partials that a walk keeps in registers (two waves per SIMD, which the LDS allows, have
+// 256 each; the kernel then uses all of them)
 #ifndef RGD_WALK_REGS
 #define RGD_WALK_REGS 5
 #endif
@@ -418,6 +423,7 @@ __global__ __launch_bounds__(NW * 64) void attn_prefix_kernel(AttnArgs a, bf16_t
     if (grp == 0) a.part_lse[((long long)sp * a.rows.R + vrow[nt]) * a.Hq + vhead[nt]] = split_lse(m[nt], lacc[nt][0]);
   };
   auto ends_here = [&](int nt) { return prefix_part_end(pl[nt], a.split_len) == pl[nt]; };
+  auto merges = [&](int nt) { return G <= 4 || ends_here(nt); };
   auto lse_slot = [&](int nt) { return WALK ? (wave * NQ + nt) * 16 + l16 : 0; };
   auto p0_slot = [&](int nt, int j) { return WALK ? ((wave * NQ + nt) * 4 + j) * 64 + lane : 0; };
   // WALK: ends split sp, which is not the last
@@ -437,7 +443,7 @@ __global__ __launch_bounds__(NW * 64) void attn_prefix_kernel(AttnArgs a, bf16_t
 #pragma unroll
           for (int j = 0; j < 4; ++j) walk_p[i][nt][j] = p[j];
         }
-      if (vok[nt] && (sp > kWalkRegs || !ends_here(nt))) write_part(sp, nt, p);
+      if (vok[nt] && (sp > kWalkRegs || !merges(nt))) write_part(sp, nt, p);
       if (grp == 0) walk_lse[WALK ? sp : 0][lse_slot(nt)] = lse;
       wmx[nt] = fmaxf(wmx[nt], lse);
       m[nt] = kNoRef;
@@ -506,7 +512,7 @@ __global__ __launch_bounds__(NW * 64) void attn_prefix_kernel(AttnArgs a, bf16_t
       if (!vok[nt]) continue;
       u32x4 pn[4];
       pack_split(nt, pn);
-      if (!ends_here(nt)) {
+      if (!merges(nt)) {
         write_part(ns - 1, nt, pn);
         continue;
       }
@@ -564,9 +570,16 @@ __global__ __launch_bounds__(NW * 64) void attn_prefix_kernel(AttnArgs a, bf16_t
           if (k0 + u < ns - 1) add(k0 + u, p[u]);
       }
       add(ns - 1, pn);
-      bf16_t* y0 = out + ((long long)vrow[nt] * a.Hq + vhead[nt]) * D + grp * 4;
+      const long long idx = (long long)vrow[nt] * a.Hq + vhead[nt];
+      if (ends_here(nt)) {
 #pragma unroll
-      for (int dt = 0; dt < 8; ++dt) *(u32x2*)(y0 + dt * 16) = u32x2{pack2(y[dt][0], y[dt][1]), pack2(y[dt][2], y[dt][3])};
+        for (int dt = 0; dt < 8; ++dt)
+          *(u32x2*)(out + idx * D + dt * 16 + grp * 4) = u32x2{pack2(y[dt][0], y[dt][1]), pack2(y[dt][2], y[dt][3])};
+      } else {
+#pragma unroll
+        for (int dt = 0; dt < 8; ++dt) *(f32x4*)(a.part_o + idx * D + dt * 16 + grp * 4) = y[dt];
+        if (grp == 0) a.part_lse[idx] = merged_lse(mx, d[0]);
+      }
     }
   }
 }
@@ -837,14 +850,14 @@ __global__ __launch_bounds__(256) void attn_tail_combine_kernel(AttnArgs a, floa
 // 64 59.8 / 55.6, 200 84.4 / 81.9.  The states and their merge are the same, so the
 // bits are too.
 // GM: query heads per KV head at most (LDS).
-// LIST: the rows are those of a list, left by a walk, which writes the partials of
-// the splits that a row's prefix reaches.
+// ROWS: all rows (0), or those of a list that a walk leaves, with the partials of
+// the splits that a row's prefix reaches (1) or one merged fp32 partial (2).
 constexpr int kMergeMaxSplits = 64;
 
-template <bool LIST, int NWV, int GM>
+template <int ROWS, int NWV, int GM>
 __global__ __launch_bounds__(NWV * 64) void attn_tail_merge_kernel(AttnArgs a, bf16_t* out, const int* rowlist) {
   constexpr int D = 128, TT = 32;
-  const int r = LIST ? rowlist[blockIdx.x] : blockIdx.x, g = blockIdx.y;
+  const int r = ROWS ? rowlist[blockIdx.x] : blockIdx.x, g = blockIdx.y;
   const int G = a.Hq / a.Hkv;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int l16 = lane & 15, grp = lane >> 4;
@@ -873,20 +886,29 @@ __global__ __launch_bounds__(NWV * 64) void attn_tail_merge_kernel(AttnArgs a, b
   // request those of this wave's first head now so their latency overlaps the
   // tail attention (splits beyond kPrefetch are loaded by the combine).
   const int S = a.splits;
-  constexpr int kPrefetch = NWV == 1 ? 1 : 16;
+  constexpr bool kOne = NWV == 1 || ROWS == 2;  // one partial per head
+  constexpr int kPrefetch = ROWS == 2 ? 2 : NWV == 1 ? 1 : 16;
   const long long pstep = R * a.Hq * D;
   // (Loads in this kernel are unconditional, from clamped addresses, and
   // masked afterwards: a predicated load makes the compiler wait for it where
   // the branches join, one memory round trip each.)
   // (a wave past the G heads loads head G-1's and does not use them)
-  uint32_t pre[kPrefetch];  // bf16 pairs
+  uint32_t pre[kPrefetch];  // bf16 pairs (ROWS 2: the two fp32 values)
   float pre_lse;
   {
     const int head = g * G + min(wave, G - 1);
-    const bf16_t* po = (const bf16_t*)a.part_o + ((long long)r * a.Hq + head) * D + part_slot(2 * lane);
+    const long long i0 = ((long long)r * a.Hq + head) * D;
+    if constexpr (ROWS == 2) {
+      const u32x2 v = *(const u32x2*)(a.part_o + i0 + 2 * lane);
+      pre[0] = v[0];
+      pre[1] = v[1];
+      pre_lse = a.part_lse[(long long)r * a.Hq + head];
+    } else {
+      const bf16_t* po = (const bf16_t*)a.part_o + i0 + part_slot(2 * lane);
 #pragma unroll
-    for (int k = 0; k < kPrefetch; ++k) pre[k] = *(const uint32_t*)(po + min(k, S - 1) * pstep);
-    pre_lse = a.part_lse[((long long)min(lane, S - 1) * R + r) * a.Hq + head];
+      for (int k = 0; k < kPrefetch; ++k) pre[k] = *(const uint32_t*)(po + min(k, S - 1) * pstep);
+      pre_lse = a.part_lse[((long long)min(lane, S - 1) * R + r) * a.Hq + head];
+    }
   }
 
   u32x4 qf[4];
@@ -900,7 +922,7 @@ __global__ __launch_bounds__(NWV * 64) void attn_tail_merge_kernel(AttnArgs a, b
     }
   }
   const int pe = prefix_part_end(plen, a.split_len);
-  const int nsp = LIST ? (pe + a.split_len - 1) / a.split_len : S;  // splits with a partial
+  const int nsp = ROWS == 1 ? (pe + a.split_len - 1) / a.split_len : S;  // splits with a partial
   // o += the split partials of a head by their weights (lane k holds split k's), in
   // split order; a split without positions is left out
   auto add_splits = [&](const bf16_t* po, float lses, float w, float inv, bool first, float& o0, float& o1) {
@@ -914,6 +936,10 @@ __global__ __launch_bounds__(NWV * 64) void attn_tail_merge_kernel(AttnArgs a, b
 #pragma unroll
       for (int k = 0; k < kPrefetch; ++k)
         if (k < nsp) add(k, pre[k]);
+    }
+    if (S == 1) {
+      if (!first) add(0, *(const uint32_t*)po);
+      return;
     }
     // eight splits' loads at a time
     for (int k0 = first ? kPrefetch : 0; k0 < nsp; k0 += 8) {
@@ -936,17 +962,25 @@ __global__ __launch_bounds__(NWV * 64) void attn_tail_merge_kernel(AttnArgs a, b
   // flight.  Lane sp holds split sp's log-sum-exp.
   float s_lse = -INFINITY, s_o0 = 0.f, s_o1 = 0.f;
   auto combine_splits = [&](int head, float lses, bool first) {
-    if (NWV == 1 || S == 1) {  // its weight is 1 (every lane holds its log-sum-exp)
-      const uint32_t v = first ? pre[0] : *(const uint32_t*)((const bf16_t*)a.part_o + ((long long)r * a.Hq + head) * D + part_slot(2 * lane));
+    if (kOne || S == 1) {  // its weight is 1 (every lane holds its log-sum-exp)
       s_lse = lses;
-      s_o0 = __uint_as_float(v << 16);
-      s_o1 = __uint_as_float(v & 0xFFFF0000u);
+      const long long i0 = ((long long)r * a.Hq + head) * D;
+      if constexpr (ROWS == 2) {
+        u32x2 v = {pre[0], pre[1]};
+        if (!first) v = *(const u32x2*)(a.part_o + i0 + 2 * lane);
+        s_o0 = __uint_as_float(v[0]);
+        s_o1 = __uint_as_float(v[1]);
+      } else {
+        const uint32_t v = first ? pre[0] : *(const uint32_t*)((const bf16_t*)a.part_o + i0 + part_slot(2 * lane));
+        s_o0 = __uint_as_float(v << 16);
+        s_o1 = __uint_as_float(v & 0xFFFF0000u);
+      }
       return;
     }
     lses = lane < nsp ? lses : -INFINITY;
     const float mx = wave_max(lses), w = split_weight(lses, mx), den = butterfly(w);
     const float inv = den > 0.f ? 1.f / den : 0.f;
-    s_lse = den > 0.f ? mx + __logf(den) : -INFINITY;
+    s_lse = merged_lse(mx, den);
     s_o0 = s_o1 = 0.f;
     add_splits((const bf16_t*)a.part_o + ((long long)r * a.Hq + head) * D + part_slot(2 * lane), lses, w, inv, first, s_o0, s_o1);
   };
@@ -1085,7 +1119,7 @@ __global__ __launch_bounds__(NWV * 64) void attn_tail_merge_kernel(AttnArgs a, b
       }
     }
     const float tail_lse = tl > 0.f ? (tm + __log2f(tl)) * kLn2 : -INFINITY;
-    if (NWV == 1 || h < 4) {  // the prefix splits are combined already: two partials left
+    if (kOne || h < 4) {  // the prefix splits are combined already: two partials left
       const float mx = fmaxf(s_lse, tail_lse);
       const float ws = s_lse == -INFINITY ? 0.f : __expf(s_lse - mx);
       const float wt = tail_lse == -INFINITY ? 0.f : __expf(tail_lse - mx);
@@ -1100,7 +1134,7 @@ __global__ __launch_bounds__(NWV * 64) void attn_tail_merge_kernel(AttnArgs a, b
     const float ls = lane < nsp ? lses : -INFINITY;
     const float mx = wave_max(fmaxf(ls, tail_lse));
     const float w = split_weight(ls, mx), wt = split_weight(tail_lse, mx);
-    const float den = butterfly(w) + wt;
+    const float den = (S == 1 ? split_weight(lses, mx) : butterfly(w)) + wt;
     const float inv = den > 0.f ? 1.f / den : 0.f;
     const float ft = tl > 0.f ? wt * inv / tl : 0.f;  // applied to the unnormalised tail sum
     float o0 = ft * to0, o1 = ft * to1;
@@ -1110,8 +1144,8 @@ __global__ __launch_bounds__(NWV * 64) void attn_tail_merge_kernel(AttnArgs a, b
   if (wave < G) finish(wave, 0.f);
   for (int h = wave + NWV; h < G; h += NWV) {  // further heads
     const int head = g * G + h;
-    const float lses = a.part_lse[((long long)min(lane, S - 1) * R + r) * a.Hq + head];
-    if (NWV == 1 || h < 4) combine_splits(head, lses, false);
+    const float lses = a.part_lse[((long long)(ROWS == 2 ? 0 : min(lane, S - 1)) * R + r) * a.Hq + head];
+    if (kOne || h < 4) combine_splits(head, lses, false);
     finish(h, lses);
   }
 }
@@ -1181,14 +1215,15 @@ hipError_t attn_tail_merge_bf16(const AttnArgs& a, bf16_t* out, hipStream_t s) {
   // to merge per head (with 16 splits of an 8193-position prompt the serial loads of
   // four heads' partials cost more: 117 against 111 us)
   const int G = a.Hq / a.Hkv;
-  const bool one = G <= 4 && a.splits == 1 && (long long)rows * a.Hkv >= 2048;
+  const bool one = G <= 4 && (a.walk || a.splits == 1) && (long long)rows * a.Hkv >= 2048;
   const dim3 grid(rows, a.Hkv);
   if (a.walk) {
-    if (one) hipLaunchKernelGGL((attn_tail_merge_kernel<true, 1, 4>), grid, dim3(64), 0, s, a, out, a.left);
-    else hipLaunchKernelGGL((attn_tail_merge_kernel<true, 4, 16>), grid, dim3(256), 0, s, a, out, a.left);
+    if (one) hipLaunchKernelGGL((attn_tail_merge_kernel<2, 1, 4>), grid, dim3(64), 0, s, a, out, a.left);
+    else if (G <= 4) hipLaunchKernelGGL((attn_tail_merge_kernel<2, 4, 4>), grid, dim3(256), 0, s, a, out, a.left);
+    else hipLaunchKernelGGL((attn_tail_merge_kernel<1, 4, 16>), grid, dim3(256), 0, s, a, out, a.left);
   } else {
-    if (one) hipLaunchKernelGGL((attn_tail_merge_kernel<false, 1, 4>), grid, dim3(64), 0, s, a, out, nullptr);
-    else hipLaunchKernelGGL((attn_tail_merge_kernel<false, 4, 16>), grid, dim3(256), 0, s, a, out, nullptr);
+    if (one) hipLaunchKernelGGL((attn_tail_merge_kernel<0, 1, 4>), grid, dim3(64), 0, s, a, out, nullptr);
+    else hipLaunchKernelGGL((attn_tail_merge_kernel<0, 4, 16>), grid, dim3(256), 0, s, a, out, nullptr);
   }
   return hipGetLastError();
 }

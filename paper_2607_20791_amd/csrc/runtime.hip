@@ -335,13 +335,14 @@ struct RowArrays {
 // registers and LDS and most rows need no tail kernel, but it runs its tiles one after
 // the other on few CUs.  Costs in units of 0.01 us, fitted to 450 measured chunks (1
 // to 8 KV heads, 1 to 8 query heads each, 64-2048 rows, one to eight prompts, up to 8048
-// positions; the side taken is 0.3% slower than the better one on average, 14% at worst):
-// a walk's launch, 130 per 64-position tile and 148 per split in each round of 256
-// workgroups, then the tail kernel for the rows left; a launch of split workgroups, 88
+// positions; the side taken is 0.3% slower than the better one on average, 18% at worst):
+// a walk's launch, 125 per 64-position tile and 150 per split in each round of 256
+// workgroups, then the tail kernel for the rows left (with more than four query heads per
+// KV head it merges their partials); a launch of split workgroups, 88
 // per tile and round, then the tail kernel for all rows and their partials.
 // Attention stage, us, split / walk, one prompt, 32 query and 8 KV heads: 256 rows
-// after 1000 positions 50 / 67, 512 86 / 91, 1024 184 / 137 and after 6000 267 / 201,
-// 2048 rows after 3000 456 / 269; 8 and 2 heads: 2048 rows after 3000 177 / 221.
+// after 1000 positions 51 / 63, 512 87 / 84, 1024 184 / 108 and after 6000 265 / 195,
+// 2048 rows after 3000 454 / 246; 8 and 2 heads: 1024 rows after 1000 81 / 133.
 void plan_walk(const rgd_model* m, const rgd_kv* kv, HostRows& h) {
   h.walk = false;
   h.left.clear();
@@ -351,14 +352,14 @@ void plan_walk(const rgd_model* m, const rgd_kv* kv, HostRows& h) {
     if (prefix_part_end(h.plen[r], len) != h.plen[r]) h.left.push_back((int)r);
   const long long R = (long long)h.plen.size(), Hkv = m->cfg.n_kv_heads, Hq = m->cfg.n_heads;
   const long long S = cdiv(h.maxplen, len), left = (long long)h.left.size();
-  long long walk = left * Hkv + left * Hq * S / 200;
+  long long walk = Hq <= 4 * Hkv ? left * Hkv / 2 : left * Hkv + left * Hq * S / 200;
   long long split = 7 * R * Hkv / 10 + 18 * R * S * Hq / 1000;
   for (size_t b0 = 0; b0 < h.blocks.size(); b0 += kAttnInlineBlocks) {  // one launch of the kernel
     const size_t nb = std::min<size_t>(kAttnInlineBlocks, h.blocks.size() - b0);
     int longest = 0;
     for (size_t i = 0; i < nb; ++i) longest = std::max(longest, h.blocks[b0 + i].w);
     const long long tiles = cdiv(longest, 64), ns = cdiv(longest, len);
-    walk += 1460 + cdiv((long long)nb * Hkv, 256) * (130 * tiles + 148 * ns);
+    walk += 1460 + cdiv((long long)nb * Hkv, 256) * (125 * tiles + 150 * ns);
     split += 1620 + cdiv((long long)nb * Hkv * ns, 256) * 88 * std::min<long long>(len / 64, tiles);
   }
   h.walk = walk < split;

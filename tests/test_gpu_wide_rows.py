@@ -55,7 +55,8 @@ def _prefill(rgd, t, world, dims, tokens, max_rows):
 # prompts in one chunk, with prefix splits of one and of three 64-position tiles.
 # The attention walks over the prefix splits in the wide runs of 690, 2600 (eight query heads) and, with 32
 # query heads, of 2100 (66 row blocks, two launches; splits of two tiles, 17 of them: partials in LDS,
-# registers and memory), 1300 (eight heads per KV head) and 2560 rows (16; 40 splits).  In runs of
+# registers and memory), 1300 (eight heads per KV head), 2560 (16; 40 splits) and 200 rows (few rows
+# left for the tail kernel), and in those of 150 and 70, which have one split.  In runs of
 # 64 rows at a time it does so in the first 64 positions only.  The chunks of 150 and
 # 70 rows: last rows that go through the LM head prompt by prompt's chunk (held back, in two lots for 70
 # prompts) and in place.
@@ -65,7 +66,7 @@ CASES = [((1024, 2816, 8, 4, 512), 1, 257, 300), ((1024, 5632, 8, 2, 512), 1, 70
          ((4096, 1152, 32, 8, 512), 3, 230, 700), ((1024, 1408, 8, 8, 512), 2, 1300, 2600),
          ((1024, 1408, 8, 2, 512), 1, 1300, 1300), ((1024, 1408, 8, 2, 512), 1, 1000, 1000),
          ((1024, 1408, 32, 8, 512), 1, 2100, 2100), ((1024, 128, 32, 4, 512), 1, 1300, 1300),
-         ((1024, 128, 32, 2, 512), 1, 2560, 2560),
+         ((1024, 128, 32, 2, 512), 1, 2560, 2560), ((1024, 128, 32, 8, 512), 4, 200, 256),
          ((1024, 128, 8, 2, 512), 5, 30, 150), ((1024, 128, 8, 2, 512), 70, 1, 70)]
 
 
