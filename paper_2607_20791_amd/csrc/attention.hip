@@ -841,13 +841,16 @@ __global__ __launch_bounds__(256) void attn_tail_combine_kernel(AttnArgs a, floa
 // form.  The prefix-split partials of heads 0 .. 3 are combined into one first (of
 // the wave's first head while its first tile is loading), which leaves a two-term merge
 // with the tail after the exchange; the partials of further heads (G > 4) and their
-// tail are merged in one go.
+// tail are merged in one go, eight splits' loads at a time (64 rows of an 8193-position
+// prompt, 16 splits, 8 query heads per KV head, 64 tail positions: 48.7 us with the
+// prefix kernel, 53 one load at a time).
 // NWV: waves per workgroup.  Four take one lane of work each: the shortest chain,
 // for few (row, head) pairs.  One takes all four in turn: a workgroup's start and
 // merge cost more than a tile, and with enough pairs to fill the chip fewer, longer
 // waves pay them once instead of four times.  Attention stage of 256 rows x 8 KV heads
 // over 1024-position prompts, four waves / one: tails of 4 positions 56.9 / 47.9 us,
-// 64 59.8 / 55.6, 200 84.4 / 81.9.  The states and their merge are the same, so the
+// 64 59.8 / 55.6, 200 84.4 / 81.9 (4.2 less since one wave takes rows of one partial
+// only and fewer registers: 78.2 to 74.0 in the attention entry point).  The states and their merge are the same, so the
 // bits are too.
 // GM: query heads per KV head at most (LDS).
 // ROWS: all rows (0), or those of a list that a walk leaves, with the partials of
@@ -923,12 +926,13 @@ __global__ __launch_bounds__(NWV * 64) void attn_tail_merge_kernel(AttnArgs a, b
   }
   const int pe = prefix_part_end(plen, a.split_len);
   const int nsp = ROWS == 1 ? (pe + a.split_len - 1) / a.split_len : S;  // splits with a partial
+  auto lane_of = [&](float v, int k) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), k)); };
   // o += the split partials of a head by their weights (lane k holds split k's), in
   // split order; a split without positions is left out
   auto add_splits = [&](const bf16_t* po, float lses, float w, float inv, bool first, float& o0, float& o1) {
     auto add = [&](int k, uint32_t v) {
-      if (__int_as_float(__builtin_amdgcn_readlane(__float_as_int(lses), k)) == -INFINITY) return;  // uniform
-      const float wk = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), k)) * inv;
+      if (lane_of(lses, k) == -INFINITY) return;  // uniform
+      const float wk = lane_of(w, k) * inv;
       o0 = fmaf(wk, __uint_as_float(v << 16), o0);
       o1 = fmaf(wk, __uint_as_float(v & 0xFFFF0000u), o1);
     };
@@ -951,7 +955,14 @@ __global__ __launch_bounds__(NWV * 64) void attn_tail_merge_kernel(AttnArgs a, b
         if (k0 + k < nsp) add(k0 + k, v[k]);
     }
   };
-  auto butterfly = [&](float v) {
+  // maximum and sum over the lanes, which hold -inf and 0 from lane nsp on; up to four
+  // lanes are read out, in the order of the butterfly
+  auto lane_max = [&](float v) {
+    if (S <= 4) return fmaxf(fmaxf(lane_of(v, 0), lane_of(v, 1)), fmaxf(lane_of(v, 2), lane_of(v, 3)));
+    return wave_max(v);
+  };
+  auto lane_sum = [&](float v) {
+    if (S <= 4) return (lane_of(v, 0) + lane_of(v, 2)) + (lane_of(v, 1) + lane_of(v, 3));
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
     return v;
@@ -978,7 +989,7 @@ __global__ __launch_bounds__(NWV * 64) void attn_tail_merge_kernel(AttnArgs a, b
       return;
     }
     lses = lane < nsp ? lses : -INFINITY;
-    const float mx = wave_max(lses), w = split_weight(lses, mx), den = butterfly(w);
+    const float mx = lane_max(lses), w = split_weight(lses, mx), den = lane_sum(w);
     const float inv = den > 0.f ? 1.f / den : 0.f;
     s_lse = merged_lse(mx, den);
     s_o0 = s_o1 = 0.f;
@@ -1132,9 +1143,9 @@ __global__ __launch_bounds__(NWV * 64) void attn_tail_merge_kernel(AttnArgs a, b
       return;
     }
     const float ls = lane < nsp ? lses : -INFINITY;
-    const float mx = wave_max(fmaxf(ls, tail_lse));
+    const float mx = fmaxf(lane_max(ls), tail_lse);
     const float w = split_weight(ls, mx), wt = split_weight(tail_lse, mx);
-    const float den = (S == 1 ? split_weight(lses, mx) : butterfly(w)) + wt;
+    const float den = lane_sum(w) + wt;
     const float inv = den > 0.f ? 1.f / den : 0.f;
     const float ft = tl > 0.f ? wt * inv / tl : 0.f;  // applied to the unnormalised tail sum
     float o0 = ft * to0, o1 = ft * to1;
