@@ -124,6 +124,8 @@ constexpr int kMaxWalkSplits = 40;
 #define RGD_WALK_REGS 5
 #endif
 constexpr int kWalkRegs = RGD_WALK_REGS;
+static_assert(kWalkRegs >= 1, "merged fp32 partials take the place of the bf16 partials of splits 0 and 1");
+static_assert(kMaxWalkSplits <= 48, "the walk adds its weights as 16 sums of three");
 
 template <int NW, int NQ, bool WALK>
 __global__ __launch_bounds__(NW * 64) void attn_prefix_kernel(AttnArgs a, bf16_t* out) {
